@@ -56,21 +56,22 @@ __device__ __forceinline__ void dgrad(const void* wl, const float (&dl)[RT][4],
       for (int i = 0; i < 4; ++i) dp[mt][i] = acc[0][mt][i];
     }
   } else {
-    const float* W = reinterpret_cast<const float*>(wl);
-    constexpr int P = H + 1;
+    // slot (kb, g) is row (kb/4)*16 + 4g + kb%4 of layer l: accumulator
+    // dl[kb/4][kb%4] of this lane
+    constexpr int P = f32_pitch(H);
     const int g = lane >> 4, c = lane & 15;
+    const float* W = reinterpret_cast<const float*>(wl) + 4 * g * P + c;
+    f32x4 acc[MTP];
+    mfma_rows_f32<MTP, RT>(
+        [&](int mt, int kq) {
+          const float* w = W + kq * 16 * P + mt * 16;
+          return f32x4{w[0], w[P], w[2 * P], w[3 * P]};
+        },
+        [&](int kq, int i) { return dl[kq][i]; }, acc);
 #pragma unroll
-    for (int mt = 0; mt < MTP; ++mt) {
-      f32x4 acc = zero4();
+    for (int mt = 0; mt < MTP; ++mt)
 #pragma unroll
-      for (int kb = 0; kb < 4 * RT; ++kb) {
-        // row R of layer l fed by slot (kb, g): accumulator dl[kb/4][kb%4]
-        const int R = (kb >> 2) * 16 + 4 * g + (kb & 3);
-        acc = mfma_f32_4(W[R * P + mt * 16 + c], dl[kb >> 2][kb & 3], acc);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) dp[mt][i] = acc[i];
-    }
+      for (int i = 0; i < 4; ++i) dp[mt][i] = acc[mt][i];
   }
 }
 
@@ -196,17 +197,21 @@ __device__ __forceinline__ void wgrad_tiles(const S* dst, const S* hst, const in
       }
     }
   } else {
+    // lane group g takes vertices vb*16 + 4g .. + 3, one 16-byte read per row
 #pragma unroll
-    for (int vb = 0; vb < NV / 4; ++vb) {
-      float hb[NC];
+    for (int vb = 0; vb < NV / 16; ++vb) {
+      f32x4 hb[NC];
 #pragma unroll
-      for (int ct = 0; ct < NC; ++ct) hb[ct] = hst[(ct * 16 + c) * SP + vb * 4 + g];
+      for (int ct = 0; ct < NC; ++ct)
+        hb[ct] = *reinterpret_cast<const f32x4*>(hst + (ct * 16 + c) * SP + vb * 16 + 4 * g);
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
         if (r < nrt) {
-          float da = dst[(rt[r] * 16 + c) * SP + vb * 4 + g];
+          const f32x4 da = *reinterpret_cast<const f32x4*>(dst + (rt[r] * 16 + c) * SP + vb * 16 + 4 * g);
 #pragma unroll
-          for (int ct = 0; ct < NC; ++ct) acc[r][ct] = mfma_f32_4(da, hb[ct], acc[r][ct]);
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int ct = 0; ct < NC; ++ct) acc[r][ct] = mfma_f32_4(da[i], hb[ct][i], acc[r][ct]);
         }
       }
     }
@@ -233,84 +238,55 @@ struct Own {
   __device__ __forceinline__ static int ct(int wave, int j) { return ROW ? j % CT : wave % CT; }
 };
 
+// A wave's operand of one block of staged vertices: row row*16 + c, vertices
+// vb*32 + 8g .. + 7 (BF16) or vb*16 + 4g .. + 3 (FP32): one 16-byte read.
 template <int PREC, typename S, int SP>
 __device__ __forceinline__ auto stage_operand(const S* st, int row, int vb, int g, int c) {
   if constexpr (PREC == 1) return *reinterpret_cast<const bf16x8*>(st + (row * 16 + c) * SP + vb * 32 + 8 * g);
-  else return st[(row * 16 + c) * SP + vb * 4 + g];
+  else return *reinterpret_cast<const f32x4*>(st + (row * 16 + c) * SP + vb * 16 + 4 * g);
 }
 
-// acc[j] += D[rows of rt(j)][v] * Hs[cols of ct(j)][v]^T over NV staged vertices
+// acc[j] += D[rows of rt(j)][v] * Hs[cols of ct(j)][v]^T over NV staged
+// vertices. The operands of vertex block vb + 1 are read while block vb is
+// multiplied (two register sets), so the LDS latency overlaps the MFMAs.
 template <int PREC, typename S, int SP, int RT, int CT, int NW, int NV>
 __device__ __forceinline__ void wgrad_own(const S* dst, const S* hst, f32x4 (&acc)[Own<RT, CT, NW>::TPW],
                                           int wave, int lane) {
   typedef Own<RT, CT, NW> O;
   typedef decltype(stage_operand<PREC, S, SP>(dst, 0, 0, 0, 0)) Op;
   const int g = lane >> 4, c = lane & 15;
-  constexpr int VB = PREC == 1 ? NV / 32 : NV / 4;
-  if constexpr (PREC == 1) {
-    // BF16: the operands of vertex block vb + 1 are read while block vb is
-    // multiplied (two register sets), so the LDS latency overlaps the MFMAs
-    constexpr int NH_ = O::ROW ? CT : 1, ND = O::ROW ? O::NRW : O::TPW;
-    struct Ops { Op h[NH_]; Op d[ND]; };
-    auto load = [&](int vb, Ops& o) {
-      if constexpr (O::ROW) {
+  constexpr int VB = PREC == 1 ? NV / 32 : NV / 16;
+  constexpr int NH_ = O::ROW ? CT : 1, ND = O::ROW ? O::NRW : O::TPW;
+  struct Ops { Op h[NH_]; Op d[ND]; };
+  auto load = [&](int vb, Ops& o) {
+    if constexpr (O::ROW) {
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) o.h[ct] = stage_operand<PREC, S, SP>(hst, ct, vb, g, c);
+      for (int ct = 0; ct < CT; ++ct) o.h[ct] = stage_operand<PREC, S, SP>(hst, ct, vb, g, c);
 #pragma unroll
-        for (int r = 0; r < O::NRW; ++r)
-          if (O::rt(wave, r * CT) < RT) o.d[r] = stage_operand<PREC, S, SP>(dst, O::rt(wave, r * CT), vb, g, c);
-      } else {
-        o.h[0] = stage_operand<PREC, S, SP>(hst, O::ct(wave, 0), vb, g, c);
+      for (int r = 0; r < O::NRW; ++r)
+        if (O::rt(wave, r * CT) < RT) o.d[r] = stage_operand<PREC, S, SP>(dst, O::rt(wave, r * CT), vb, g, c);
+    } else {
+      o.h[0] = stage_operand<PREC, S, SP>(hst, O::ct(wave, 0), vb, g, c);
 #pragma unroll
-        for (int j = 0; j < O::TPW; ++j)
-          if (O::rt(wave, j) < RT) o.d[j] = stage_operand<PREC, S, SP>(dst, O::rt(wave, j), vb, g, c);
-      }
-    };
-    Ops ops[2];
-    load(0, ops[0]);
-#pragma unroll
-    for (int vb = 0; vb < VB; ++vb) {
-      if (vb + 1 < VB) load(vb + 1, ops[(vb + 1) & 1]);
-      const Ops& o = ops[vb & 1];
-      if constexpr (O::ROW) {
-#pragma unroll
-        for (int r = 0; r < O::NRW; ++r)
-          if (O::rt(wave, r * CT) < RT)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) acc[r * CT + ct] = mfma_bf16_32(o.d[r], o.h[ct], acc[r * CT + ct]);
-      } else {
-#pragma unroll
-        for (int j = 0; j < O::TPW; ++j)
-          if (O::rt(wave, j) < RT) acc[j] = mfma_bf16_32(o.d[j], o.h[0], acc[j]);
-      }
+      for (int j = 0; j < O::TPW; ++j)
+        if (O::rt(wave, j) < RT) o.d[j] = stage_operand<PREC, S, SP>(dst, O::rt(wave, j), vb, g, c);
     }
-    return;
-  }
+  };
+  Ops ops[2];
+  load(0, ops[0]);
 #pragma unroll
   for (int vb = 0; vb < VB; ++vb) {
-    if constexpr (O::ROW) {
-      Op hb[CT];
+    if (vb + 1 < VB) load(vb + 1, ops[(vb + 1) & 1]);
+    const Ops& o = ops[vb & 1];
+    constexpr int NI = PREC == 1 ? 1 : 4;   // contraction steps of a block
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) hb[ct] = stage_operand<PREC, S, SP>(hst, ct, vb, g, c);
-#pragma unroll
-      for (int r = 0; r < O::NRW; ++r) {
-        if (O::rt(wave, r * CT) < RT) {
-          const Op da = stage_operand<PREC, S, SP>(dst, O::rt(wave, r * CT), vb, g, c);
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            if constexpr (PREC == 1) acc[r * CT + ct] = mfma_bf16_32(da, hb[ct], acc[r * CT + ct]);
-            else acc[r * CT + ct] = mfma_f32_4(da, hb[ct], acc[r * CT + ct]);
-          }
-        }
-      }
-    } else {
-      const Op hb = stage_operand<PREC, S, SP>(hst, O::ct(wave, 0), vb, g, c);
+    for (int i = 0; i < NI; ++i) {
 #pragma unroll
       for (int j = 0; j < O::TPW; ++j) {
+        const int r = O::ROW ? j / CT : j, ct = O::ROW ? j % CT : 0;
         if (O::rt(wave, j) < RT) {
-          const Op da = stage_operand<PREC, S, SP>(dst, O::rt(wave, j), vb, g, c);
-          if constexpr (PREC == 1) acc[j] = mfma_bf16_32(da, hb, acc[j]);
-          else acc[j] = mfma_f32_4(da, hb, acc[j]);
+          if constexpr (PREC == 1) acc[j] = mfma_bf16_32(o.d[r], o.h[ct], acc[j]);
+          else acc[j] = mfma_f32_4(o.d[r][i], o.h[ct][i], acc[j]);
         }
       }
     }

@@ -304,7 +304,7 @@ struct NetF32 {
   static constexpr int MTH = H / 16, MTO = K / 2 + SEL, KQ = K / 4;
   static constexpr int CH = 64;              // rows per LDS chunk
   static constexpr int TPC = CH / 16;        // row tiles per chunk
-  static constexpr int PH = H + 1;           // pitch of hidden and output layers
+  static constexpr int PH = f32_pitch(H);    // pitch of hidden and output layers
   static constexpr int P0 = M::IN + 1;       // pitch of layer 0
   static constexpr int BUF = (CH * PH > H * P0) ? CH * PH : H * P0;
   static constexpr int SP = kWGV + 4;

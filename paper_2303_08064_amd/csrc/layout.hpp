@@ -106,11 +106,18 @@ struct Bf16Layout {
   NASG_HD int64_t total_elems() const { return bwd_sel_off() + (int64_t)16 * d.S * d.H; }
 };
 
+// pitch of the FP32 hidden and output layers
+NASG_HD constexpr int f32_pitch(int H) { return H + 4; }
+
 // ---- FP32 row-major layout (elements are float) ----
-// layer l: [rows][cols_pad + 1] with cols_pad = 16 or 64 (l == 0) or H; output rows in physical order
+// layer l: [rows][pitch], pitch 16 + 1 or 64 + 1 (l == 0) or H + 4; output
+// rows in physical order. H + 4 keeps rows 16-byte aligned, and its reads are
+// free of LDS bank conflicts both ways: the forward's 16-byte reads (lane
+// (g, c): row c, columns 4g ..: 16 lanes c cover the 64 banks) and the
+// backward's 4-byte ones (row 4g, column c: bank 16g + c).
 struct F32Layout {
   NetDims d;
-  NASG_HD int pitch(int l) const { return (l == 0 ? d.in_pad() : d.H) + 1; }
+  NASG_HD int pitch(int l) const { return l == 0 ? d.in_pad() + 1 : f32_pitch(d.H); }
   NASG_HD int64_t off(int l) const {
     if (l == 0) return 0;
     return (int64_t)d.H * pitch(0) + (int64_t)(l - 1) * d.H * pitch(1);

@@ -274,7 +274,7 @@ struct Mlp<H, K, 1, E> {
 };
 
 // ---------------------------------------------------------------- FP32 ----
-// 16x16x4 f32 MFMA; weights row-major in LDS with an odd pitch.
+// 16x16x4 f32 MFMA; weights row-major in LDS (F32Layout).
 template <int H, int K, int E>
 struct Mlp<H, K, 0, E> {
   static constexpr int MTH = H / 16;
@@ -351,21 +351,21 @@ struct Mlp<H, K, 0, E> {
     }
   }
 
-  // out = W in; W row-major [MT*16][H+1] at `lds`, input neuron of slot (kb, g)
-  // is (kb/4)*16 + 4g + kb%4 = accumulator in[kb/4][kb%4] of this lane
+  // out = W in; W row-major [MT*16][pitch] at `lds`, input neuron of slot
+  // (kb, g) is (kb/4)*16 + 4g + kb%4 = accumulator in[kb/4][kb%4] of this lane
   template <int MT>
   __device__ __forceinline__ static void gemm(const float* lds, const float (&in)[MTH][4], float (&out)[MT][4], int lane) {
     const int g = lane >> 4, c = lane & 15;
-    constexpr int P = H + 1;
+    constexpr int P = f32_pitch(H);
+    const float* row = lds + c * P + 4 * g;
+    f32x4 acc[MT];
+    mfma_rows_f32<MT, MTH>(
+        [&](int mt, int kq) { return *reinterpret_cast<const f32x4*>(row + mt * 16 * P + kq * 16); },
+        [&](int kq, int i) { return in[kq][i]; }, acc);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      f32x4 acc = zero4();
-      const float* row = lds + (mt * 16 + c) * P + 4 * g;
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int kb = 0; kb < 4 * MTH; ++kb) acc = mfma_f32_4(row[(kb >> 2) * 16 + (kb & 3)], in[kb >> 2][kb & 3], acc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[mt][i] = acc[i];
-    }
+      for (int i = 0; i < 4; ++i) out[mt][i] = acc[mt][i];
   }
 };
 

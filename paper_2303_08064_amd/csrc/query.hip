@@ -18,11 +18,13 @@ namespace nasg {
 
 // The hidden-64 BF16 networks' queries sample one vertex per lane (four
 // blocks per wave pass; the four blocks' lobes take 144 registers, so two
-// waves per SIMD). Their FP32 queries keep one block per pass and three
-// waves per SIMD (the four blocks' lobes and the FP32 forward do not fit two
-// waves' registers); the raw forwards run one wave per SIMD; the hidden-128
-// network two, its 132 KiB of forward weights leaving room for one
-// workgroup per CU.
+// waves per SIMD). K = 8 in BF16 keeps one block per pass and three waves
+// per SIMD. The FP32 queries run one block per pass (the four blocks' lobes
+// and the FP32 forward do not fit two waves' registers) at two waves per
+// SIMD, which is what their weights leave room for: two workgroups of four
+// waves per CU (K = 4 and 8), or one of eight (K = 16, 92 KiB of weights).
+// The raw forwards run one wave per SIMD; the hidden-128 network two, its
+// 132 KiB of forward weights leaving room for one workgroup per CU.
 constexpr bool query_four(int H, int K, int MODE, int PREC) { return H == 64 && K != 8 && MODE == 0 && PREC == 1; }
 // dynamic LDS of a query launch: the weights, plus the four-block kernels'
 // two input staging buffers per wave
@@ -32,8 +34,10 @@ constexpr size_t query_dynamic_lds(int weight_bytes, bool four, int nb, int nw) 
                : (nb == 2 ? (size_t)nw * 2 * (kInFeatures + 4) * 32 * sizeof(float) : 0));
 }
 constexpr int query_waves_per_eu(int H, int K, int MODE, int PREC) {
-  return H == 64 ? (MODE == 0 ? (query_four(H, K, MODE, PREC) ? 2 : 3) : 1) : 2;
+  return H == 64 ? (MODE == 0 ? (query_four(H, K, MODE, PREC) || PREC == 0 ? 2 : 3) : 1) : 2;
 }
+// waves per workgroup of the hidden-64 networks' queries
+constexpr int query_waves(int K, int PREC) { return PREC == 0 && K == 16 ? 8 : 4; }
 
 // Records of one 16-vertex block's lobes (optional output of a query).
 template <int KQ>
@@ -334,7 +338,8 @@ static hipError_t occupancy_s(int mode, int lds_bytes, int* per_cu) {
 
 template <int H, int K, int PREC>
 static hipError_t launch_query_t(const QueryArgs& a, int mode, hipStream_t st) {
-  return a.sel ? launch_query_s<H, K, PREC, 1, 0, 1, 4>(a, mode, st) : launch_query_s<H, K, PREC, 0, 0, 1, 4>(a, mode, st);
+  constexpr int NW = query_waves(K, PREC);
+  return a.sel ? launch_query_s<H, K, PREC, 1, 0, 1, NW>(a, mode, st) : launch_query_s<H, K, PREC, 0, 0, 1, NW>(a, mode, st);
 }
 
 hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode, hipStream_t st) {
@@ -353,10 +358,10 @@ hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode
 }
 
 hipError_t query_workgroups_per_cu(const NetDims& d, int prec, int mode, int lds_bytes, int* per_cu) {
-#define NASG_CASE(h, k, p)                                                        \
-  if (d.H == h && d.K == k && prec == p && d.E == 0)                              \
-    return d.S ? occupancy_s<h, k, p, 1, 0, 1, 4>(mode, lds_bytes, per_cu)       \
-               : occupancy_s<h, k, p, 0, 0, 1, 4>(mode, lds_bytes, per_cu);
+#define NASG_CASE(h, k, p)                                                                  \
+  if (d.H == h && d.K == k && prec == p && d.E == 0)                                        \
+    return d.S ? occupancy_s<h, k, p, 1, 0, 1, query_waves(k, p)>(mode, lds_bytes, per_cu) \
+               : occupancy_s<h, k, p, 0, 0, 1, query_waves(k, p)>(mode, lds_bytes, per_cu);
   NASG_FOR_EACH_NET(NASG_CASE)
 #undef NASG_CASE
 #define NASG_CASE(h, k, p, s, e)                                 \
