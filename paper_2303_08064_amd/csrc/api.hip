@@ -133,7 +133,9 @@ struct nasg_ctx {
   Workspace ws;
   int num_cus;
   int device;
-  int q_per_cu[2];   // resident query kernel's workgroups per CU (query, raw forward)
+  // resident query kernels' workgroups per CU (query, raw forward, query with
+  // records; of a large and of a small batch)
+  int q_per_cu[3][2];
 };
 
 namespace {
@@ -216,10 +218,11 @@ nasg_status nasg_create(const nasg_config* cfg, const nasg_state* st, nasg_ctx**
   c->ws = carve(cfg);
   c->num_cus = cus > 0 ? cus : 1;
   c->device = dev;
-  c->q_per_cu[0] = c->q_per_cu[1] = 1;
+  for (auto& m : c->q_per_cu) m[0] = m[1] = 1;
   if (query_is_resident(c->d, cfg->precision)) {
-    for (int mode = 0; mode < 2 && e == hipSuccess; ++mode)
-      e = query_workgroups_per_cu(c->d, cfg->precision, mode, (int)query_lds_bytes(cfg), &c->q_per_cu[mode]);
+    for (int i = 0; i < 6 && e == hipSuccess; ++i)
+      e = query_workgroups_per_cu(c->d, cfg->precision, i >> 1, i & 1, (int)query_lds_bytes(cfg),
+                                  &c->q_per_cu[i >> 1][i & 1]);
     if (e != hipSuccess) {
       delete c;
       return hip_fail(fn, e);
@@ -280,6 +283,7 @@ static nasg_status run_query(nasg_ctx* ctx, const char* fn, const float* feat, c
   } else {
     NASG_TRY(check_ptr(fn, raw_out, "raw_out"));
   }
+  if (rec_out != nullptr) mode = 2;   // the query kernel that also stores the decoded records
   QueryArgs a;
   a.wpack = ctx->st.wpack;
   a.lds_bytes = (int)query_lds_bytes(&ctx->cfg);
@@ -297,7 +301,8 @@ static nasg_status run_query(nasg_ctx* ctx, const char* fn, const float* feat, c
   a.sel = ctx->d.S;
   a.amul = ctx->cfg.isotropic ? 0.0f : 1.0f;
   a.num_cus = ctx->num_cus;
-  a.per_cu = ctx->q_per_cu[mode];
+  a.per_cu[0] = ctx->q_per_cu[mode][0];
+  a.per_cu[1] = ctx->q_per_cu[mode][1];
   hipError_t e = query_is_resident(ctx->d, ctx->cfg.precision)
                      ? launch_query(a, ctx->d, ctx->cfg.precision, mode, (hipStream_t)stream)
                      : launch_large_query(a, ctx->d, ctx->cfg.precision, mode, (hipStream_t)stream);

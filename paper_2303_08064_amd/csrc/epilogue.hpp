@@ -19,25 +19,6 @@ __device__ __forceinline__ void lobe_raw(const float (&out)[MTO][4], int q, floa
   }
 }
 
-// log-sum-exp of the K mixture logits (softmax of Tab. "decoding")
-template <int KQ, int MTO>
-__device__ __forceinline__ float logit_lse(const float (&out)[MTO][4]) {
-  float alpha[KQ];
-#pragma unroll
-  for (int q = 0; q < KQ; ++q) {
-    const int t = 7 * KQ + q;
-    alpha[q] = out[t >> 2][t & 3];
-  }
-  float mx = alpha[0];
-#pragma unroll
-  for (int q = 1; q < KQ; ++q) mx = fmaxf(mx, alpha[q]);
-  mx = quad_max(mx);
-  float se = 0.0f;
-#pragma unroll
-  for (int q = 0; q < KQ; ++q) se += fexp_sub(alpha[q], mx);
-  se = quad_sum(se);
-  return mx + flog(se);
-}
 
 // Weighted NLL of one vertex and its gradient w.r.t. the raw outputs
 // (Sec. 4.2): gs = dL/dlog q = -w/B (0 for padding lanes). Writes dl in the
@@ -103,7 +84,7 @@ __device__ __forceinline__ float train_epilogue(const float (&out)[MTO][4], floa
       dl[t >> 2][t & 3] = gq[p];
     }
   }
-  const float logq = mixture_lse<KQ, true>(ell);
+  const float logq = mixture_lse<KQ>(ell);
   float lterm = logq, gsq = gs;
   if constexpr (S == 1) {
     const int c = lane_id() & 15;
@@ -144,18 +125,19 @@ __device__ __forceinline__ float train_epilogue(const float (&out)[MTO][4], floa
   return lterm;
 }
 
-// A query's decode of one vertex's lobes (Tab. "decoding"): frames,
-// lambda, a and log c = log(A_k / K_k) into lb, the mixture weights A_k
-// (softmax of the K logits) into A.
+// A query's decode of one vertex's lobes (Tab. "decoding") into lb; the
+// mixture weights (softmax of the K logits) are A_k = ea_k inv_se; returns the
+// logits' log-sum-exp.
 template <int KQ, int MTO>
-__device__ __forceinline__ void query_decode(const float (&out)[MTO][4], float eps, Lobe (&lb)[KQ], float (&A)[KQ],
-                                             float amul) {
-  float logK[KQ], alpha[KQ];
+__device__ __forceinline__ float query_decode(const float (&out)[MTO][4], float eps, QueryLobe (&lb)[KQ],
+                                              float (&ea)[KQ], float& inv_se, float abias) {
+#pragma clang fp contract(off)
+  float alpha[KQ];
 #pragma unroll
   for (int q = 0; q < KQ; ++q) {
     float o[8];
     lobe_raw<KQ, MTO>(out, q, o);
-    logK[q] = decode_lobe_query(o, eps, lb[q], amul);
+    decode_lobe_query(o, eps, lb[q], abias);
     alpha[q] = o[7];
   }
   // mixture weights: softmax over the K logits
@@ -163,7 +145,6 @@ __device__ __forceinline__ void query_decode(const float (&out)[MTO][4], float e
 #pragma unroll
   for (int q = 1; q < KQ; ++q) mx = fmaxf(mx, alpha[q]);
   mx = quad_max(mx);
-  float ea[KQ];
   float se = 0.0f;
 #pragma unroll
   for (int q = 0; q < KQ; ++q) {
@@ -171,47 +152,131 @@ __device__ __forceinline__ void query_decode(const float (&out)[MTO][4], float e
     se += ea[q];
   }
   se = quad_sum(se);
-  const float lse = mx + flog(se);
-  const float inv_se = frcp(se);
+  inv_se = frcp(se);
 #pragma unroll
-  for (int q = 0; q < KQ; ++q) {
-    lb[q].logc = (alpha[q] - lse) - logK[q];
-    A[q] = ea[q] * inv_se;
-  }
+  for (int q = 0; q < KQ; ++q) lb[q].c *= ea[q] * inv_se;
+  return mx + flog(se);
 }
 
-// One App. C sample from lobe s, normalised to unit length.
-__device__ __forceinline__ void sample_unit(const Lobe& s, float xi0, float xi1, float xi2, float eps, float& vx,
+// One App. C sample from a query lobe, normalised to unit length.
+__device__ __forceinline__ void sample_unit(const QueryLobe& s, float xi0, float xi1, float xi2, float eps, float& vx,
                                             float& vy, float& vz) {
-  sample_lobe(s, xi0, xi1, xi2, eps, vx, vy, vz);
+  const Lobe L = {s.zx, s.zy, s.zz, s.xx, s.xy, s.xz, s.lam, s.a, 0.0f};
+  sample_lobe(L, xi0, xi1, xi2, eps, vx, vy, vz);
   const float inv = frsq(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
   vx *= inv;
   vy *= inv;
   vz *= inv;
 }
 
-// log q at a unit direction: the lane's lobes, then the vertex's 4 lanes.
+// The mixture pdf at a unit direction: sum_k c_k G_k over the lane's lobes,
+// then the vertex's 4 lanes. No running maximum is needed: the direction was
+// drawn from this mixture, so the lobe that it came from (A_k of at least
+// 2^-24 or so) has a G of about xi0 (2^-24) or more there, and what lies
+// beneath the float range is beneath the sum's rounding.
 template <int KQ>
-__device__ __forceinline__ float query_log_pdf(const Lobe (&lb)[KQ], float vx, float vy, float vz, float eps) {
-  float ell[KQ];
+__device__ __forceinline__ float query_pdf(const QueryLobe (&lb)[KQ], float vx, float vy, float vz, float eps) {
+#pragma clang fp contract(off)
+  float s = 0.0f;
 #pragma unroll
-  for (int q = 0; q < KQ; ++q) ell[q] = eval_lobe_ell(lb[q], vx, vy, vz, eps);
-  return mixture_lse<KQ>(ell);
+  for (int q = 0; q < KQ; ++q) s = fmaf(lb[q].c, eval_query_lobe(lb[q], vx, vy, vz, eps), s);
+  return quad_sum(s) * query_pdf_scale(eps);
 }
 
-// Guiding query of one vertex: decode, inverse-CDF lobe choice, App. C
-// sample, mixture pdf at the sample. Returns log q; v receives the unit
-// direction; lb receives the decoded lobes (for the optional record store).
+// Records of one 16-vertex block's lobes (optional output of a query); lse:
+// the logits' log-sum-exp.
 template <int KQ, int MTO>
-__device__ __forceinline__ float query_epilogue(const float (&out)[MTO][4], float xi_sel, float xi0, float xi1,
-                                                float xi2, float eps, int g, int c, Lobe (&lb)[KQ], float& vx,
-                                                float& vy, float& vz, float amul = 1.0f) {
-  float A[KQ];
-  query_decode<KQ, MTO>(out, eps, lb, A, amul);
-  const int ksel = select_lobe<KQ>(A, xi_sel, g, c);
-  const Lobe s = broadcast_lobe<KQ>(lb, ksel, c);
-  sample_unit(s, xi0, xi1, xi2, eps, vx, vy, vz);
-  return query_log_pdf<KQ>(lb, vx, vy, vz, eps);
+__device__ __forceinline__ void store_records(float* rec_out, const float (&out)[MTO][4], const QueryLobe (&lb)[KQ],
+                                              float lse, float eps, int64_t v, int g) {
+  constexpr int K = 4 * KQ;
+  float* base = rec_out + (v / kRecTile) * 9 * K * kRecTile + g * KQ * kRecTile + (v % kRecTile);
+  // opaque to the compiler, which otherwise keeps an address per parameter
+  // live across the whole batch loop (registers that the K = 16 kernel spills)
+  asm("" : "+v"(base));
+#pragma unroll
+  for (int q = 0; q < KQ; ++q) {
+    float o[8];
+    lobe_raw<KQ, MTO>(out, q, o);
+    const QueryLobe& L = lb[q];
+    const float loglam = fminf(fmaxf(o[5], -kLogClamp), kLogClamp);
+    const float lam = fexp(loglam);
+    // one lobe at a time: mixed by the scheduler, the K = 16 kernel spills
+    __builtin_amdgcn_sched_barrier(0);
+    const float logc = (o[7] - lse) - log_normaliser(lam, loglam, L.a, eps);
+    const float vals[9] = {L.zx, L.zy, L.zz, L.xx, L.xy, L.xz, L.lam, L.a, logc};
+#pragma unroll
+    for (int p = 0; p < 9; ++p) base[(p * K + q) * kRecTile] = vals[p];
+  }
+}
+
+// Guiding queries of NBLK 16-vertex blocks (vertices v0 + 16 b + c): decode,
+// inverse-CDF lobe choice, App. C sample, mixture pdf at the sample, stores.
+// block(b, out) writes block b's raw outputs; xi(r, i) returns uniform row r
+// of vertex v0 + i. Lane (g, c) holds lobes g*KQ .. of vertex c of every
+// block and samples one vertex, c of block g % NBLK: the chosen lobe of each
+// block moves to the lanes that sample it, and the directions go back to the
+// lanes that hold the block's lobes. Per vertex, the same operations in the
+// same order for every NBLK, so the same results bit for bit. SPLIT keeps the
+// next block's forward out of a block's decode.
+template <int KQ, int S, int NBLK, bool REC, bool SPLIT, int MTO, typename BlockFn, typename XiFn>
+__device__ __forceinline__ void query_epilogue(const QueryArgs& a, int64_t v0, int lane, BlockFn block, XiFn xi) {
+  static_assert(NBLK == 1 || NBLK == 2 || NBLK == 4, "lane groups share the blocks evenly");
+  const int g = lane >> 4, c = lane & 15;
+  const int i = (g % NBLK) * kTileV + c;   // the vertex this lane samples
+  const int64_t vi = v0 + i;
+  const bool vi_valid = vi < a.B;
+  // one block per pass reads its uniforms from global memory: requested here,
+  // used after the lobes are decoded (the others' are staged in LDS)
+  float xr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (NBLK == 1 && vi_valid) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xr[r] = xi(r, i);
+  }
+  QueryLobe lb[NBLK][KQ];
+  QueryLobe ch = {};
+  const float abias = a.amul > 0.0f ? 0.0f : -INFINITY;   // log2 of the anisotropy's factor
+#pragma unroll
+  for (int b = 0; b < NBLK; ++b) {
+    const int64_t v = v0 + b * kTileV + c;
+    const bool valid = v < a.B;
+    float out[MTO][4];
+    block(b, out);
+    float ea[KQ], inv_se;
+    const float lse = query_decode<KQ, MTO>(out, a.eps, lb[b], ea, inv_se, abias);
+    const float xs = NBLK == 1 ? xr[0] : (valid ? xi(0, b * kTileV + c) : 0.0f);
+    const int k = select_lobe<KQ>(ea, inv_se, xs, g, c);
+    const QueryLobe r = broadcast_lobe<KQ>(lb[b], k, c);
+    if (NBLK == 1 || g % NBLK == b) ch = r;
+    // selection probability c = sigmoid(o[8K]) (Tab. "decoding")
+    if (S == 1 && a.sel_out != nullptr && valid && g == 0) a.sel_out[v] = frcp(1.0f + fexp(-out[MTO - 1][0]));
+    if (REC && valid) store_records<KQ, MTO>(a.rec_out, out, lb[b], lse, a.eps, v, g);
+    if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);
+  }
+  if (NBLK > 1 && vi_valid) {
+#pragma unroll
+    for (int r = 1; r < 4; ++r) xr[r] = xi(r, i);
+  }
+  float vx, vy, vz;
+  sample_unit(ch, xr[1], xr[2], xr[3], a.eps, vx, vy, vz);
+  float pdf = 0.0f;
+#pragma unroll
+  for (int b = 0; b < NBLK; ++b) {
+    float bx = vx, by = vy, bz = vz;
+    if constexpr (NBLK > 1) {
+      const int src = b * kTileV + c;
+      bx = __shfl(vx, src);
+      by = __shfl(vy, src);
+      bz = __shfl(vz, src);
+    }
+    const float q = query_pdf<KQ>(lb[b], bx, by, bz, a.eps);
+    if (NBLK == 1 || g % NBLK == b) pdf = q;
+  }
+  if (vi_valid && g < NBLK) {
+    a.dir_out[vi] = vx;
+    a.dir_out[a.ld + vi] = vy;
+    a.dir_out[2 * a.ld + vi] = vz;
+    a.pdf_out[vi] = pdf;
+  }
 }
 
 }  // namespace nasg

@@ -43,7 +43,7 @@ struct QueryArgs {
   int sel;               // 1: the network has the selection output (8K + 1 rows)
   float amul;            // 1: NASG lobes; 0: isotropic lobes (a = 0)
   int num_cus;
-  int per_cu = 1;        // resident query kernel: workgroups per CU at this LDS footprint
+  int per_cu[2] = {1, 1};   // resident query kernels' workgroups per CU (large, small batch)
 };
 
 struct RecArgs {
@@ -127,13 +127,14 @@ struct AdamArgs {
 
 // Lobe choice by inverse CDF over k = g*KQ + q (this library's reading: the
 // smallest k with xi_sel * sum(A) < A_0 + ... + A_k; the last lobe with
-// A_k > 0 when rounding leaves none).
+// A_k > 0 when rounding leaves none), A_k = ea_k inv_se.
 template <int KQ>
-__device__ __forceinline__ int select_lobe(const float (&A)[KQ], float xi, int g, int c) {
+__device__ __forceinline__ int select_lobe(const float (&ea)[KQ], float inv_se, float xi, int g, int c) {
+#pragma clang fp contract(off)
   float cum[KQ];
   float run = 0.0f;
 #pragma unroll
-  for (int q = 0; q < KQ; ++q) { run += A[q]; cum[q] = run; }
+  for (int q = 0; q < KQ; ++q) { run = fmaf(ea[q], inv_se, run); cum[q] = run; }
   float t0 = __shfl(run, c), t1 = __shfl(run, c + 16), t2 = __shfl(run, c + 32), t3 = __shfl(run, c + 48);
   float p01 = t0 + t1, p012 = p01 + t2, total = p012 + t3;
   float P = g == 0 ? 0.0f : (g == 1 ? t0 : (g == 2 ? p01 : p012));
@@ -151,62 +152,48 @@ __device__ __forceinline__ int select_lobe(const float (&A)[KQ], float xi, int g
     int last = -1;
 #pragma unroll
     for (int q = 0; q < KQ; ++q)
-      if (A[q] > 0.0f) last = g * KQ + q;
+      if (ea[q] * inv_se > 0.0f) last = g * KQ + q;
     last = quad_max_i(last);
     if (k == 4 * KQ) k = last < 0 ? 0 : last;
   }
   return k;
 }
 
-// s ? a : b field by field (one select per field, no branch)
-__device__ __forceinline__ Lobe select_lobe_fields(bool s, const Lobe& a, const Lobe& b) {
-  Lobe r;
-  r.zx = s ? a.zx : b.zx;
-  r.zy = s ? a.zy : b.zy;
-  r.zz = s ? a.zz : b.zz;
-  r.xx = s ? a.xx : b.xx;
-  r.xy = s ? a.xy : b.xy;
-  r.xz = s ? a.xz : b.xz;
-  r.lam = s ? a.lam : b.lam;
-  r.a = s ? a.a : b.a;
-  r.logc = s ? a.logc : b.logc;
-  return r;
-}
-
-// The selected lobe's record, from the lane group that owns it.
+// The selected lobe's fields that a sample needs, from the lane group that
+// owns it (one select per field and lobe, no branch).
 template <int KQ>
-__device__ __forceinline__ Lobe broadcast_lobe(const Lobe (&lb)[KQ], int k, int c) {
+__device__ __forceinline__ QueryLobe broadcast_lobe(const QueryLobe (&lb)[KQ], int k, int c) {
   const int gs = k / KQ, qs = k % KQ;
-  Lobe mine = lb[0];
-#pragma unroll
-  for (int q = 1; q < KQ; ++q) mine = select_lobe_fields(q == qs, lb[q], mine);
   const int src = gs * 16 + c;
-  Lobe r;
-  r.zx = __shfl(mine.zx, src);
-  r.zy = __shfl(mine.zy, src);
-  r.zz = __shfl(mine.zz, src);
-  r.xx = __shfl(mine.xx, src);
-  r.xy = __shfl(mine.xy, src);
-  r.xz = __shfl(mine.xz, src);
-  r.lam = __shfl(mine.lam, src);
-  r.a = __shfl(mine.a, src);
-  r.logc = __shfl(mine.logc, src);
+  QueryLobe r = {};
+  auto pick = [&](float QueryLobe::*f) {
+    float mine = lb[0].*f;
+#pragma unroll
+    for (int q = 1; q < KQ; ++q) mine = q == qs ? lb[q].*f : mine;
+    return __shfl(mine, src);
+  };
+  r.zx = pick(&QueryLobe::zx);
+  r.zy = pick(&QueryLobe::zy);
+  r.zz = pick(&QueryLobe::zz);
+  r.xx = pick(&QueryLobe::xx);
+  r.xy = pick(&QueryLobe::xy);
+  r.xz = pick(&QueryLobe::xz);
+  r.lam = pick(&QueryLobe::lam);
+  r.a = pick(&QueryLobe::a);
   return r;
 }
 
 // log sum_k exp(ell_k) over the lane's KQ lobes and the vertex's 4 lanes.
-// XCHG: the cross-lane steps by lane swaps (xchg_max/xchg_sum) instead of
-// LDS permutes.
-template <int KQ, bool XCHG = false>
+template <int KQ>
 __device__ __forceinline__ float mixture_lse(const float (&ell)[KQ]) {
   float m = ell[0];
 #pragma unroll
   for (int q = 1; q < KQ; ++q) m = fmaxf(m, ell[q]);
-  m = XCHG ? xchg_max(m) : quad_max(m);
+  m = xchg_max(m);
   float s = 0.0f;
 #pragma unroll
   for (int q = 0; q < KQ; ++q) s += fexp_sub(ell[q], m);
-  s = XCHG ? xchg_sum(s) : quad_sum(s);
+  s = xchg_sum(s);
   return m == -INFINITY ? -INFINITY : m + flog(s);
 }
 
@@ -214,8 +201,9 @@ hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode
 // the network's queries run the LDS-resident query kernel
 bool query_is_resident(const NetDims& d, int prec);
 // workgroups per CU of the resident query kernel (mode 0 query, 1 raw
-// forward) at `lds_bytes` of LDS; also raises the kernel's LDS limit
-hipError_t query_workgroups_per_cu(const NetDims& d, int prec, int mode, int lds_bytes, int* per_cu);
+// forward, 2 query with records; small: of the hidden-64 networks' small
+// batches) at `lds_bytes` of weights; also raises the kernel's LDS limit
+hipError_t query_workgroups_per_cu(const NetDims& d, int prec, int mode, bool small, int lds_bytes, int* per_cu);
 hipError_t launch_pdf(const RecArgs& a, int K, hipStream_t st);
 hipError_t launch_sample(const RecArgs& a, int K, hipStream_t st);
 hipError_t launch_pdf_grad(const RecArgs& a, int K, hipStream_t st);

@@ -486,7 +486,7 @@ struct DOut {
 };
 
 // ---------------------------------------------------------------- query ----
-// MODE 0: query, 1: raw forward only
+// MODE 0: query, 1: raw forward only, 2: query with the decoded records
 template <int H, int K, int PREC, int SEL, int ENC, int MODE>
 __global__ __launch_bounds__(256) void large_query_kernel(QueryArgs a) {
   typedef LargeNet<H, K, PREC, SEL, ENC> N;
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256) void large_query_kernel(QueryArgs a) {
     typename M::Input x = M::load_input(a.feat, a.ld, v, valid, g);
     float out[N::MTO][4];
     N::forward(wg, b0, b1, x, out, lane);
-    if (MODE == 1) {
+    if constexpr (MODE == 1) {
       if (valid) {
 #pragma unroll
         for (int t = 0; t < 2 * K; ++t) {
@@ -517,37 +517,17 @@ __global__ __launch_bounds__(256) void large_query_kernel(QueryArgs a) {
         }
         if (SEL == 1 && g == 0) a.raw_out[(int64_t)(8 * K) * a.ld + v] = out[N::MTO - 1][0];
       }
-      continue;
-    }
-    float xi_sel = 0.0f, xi0 = 0.0f, xi1 = 0.0f, xi2 = 0.0f;
-    if (valid) {
-      xi_sel = a.xi[v];
-      xi0 = a.xi[a.ld + v];
-      xi1 = a.xi[2 * a.ld + v];
-      xi2 = a.xi[3 * a.ld + v];
-    }
-    Lobe lb[KQ];
-    float vx, vy, vz;
-    const float logq =
-        query_epilogue<KQ, N::MTO>(out, xi_sel, xi0, xi1, xi2, a.eps, g, c, lb, vx, vy, vz, a.amul);
-    if (valid && g == 0) {
-      a.dir_out[v] = vx;
-      a.dir_out[a.ld + v] = vy;
-      a.dir_out[2 * a.ld + v] = vz;
-      a.pdf_out[v] = fexp(logq);
-      // selection probability c = sigmoid(o[8K]) (Tab. "decoding")
-      if (SEL == 1 && a.sel_out != nullptr) a.sel_out[v] = frcp(1.0f + fexp(-out[N::MTO - 1][0]));
-    }
-    if (a.rec_out != nullptr && valid) {
-      float* base = a.rec_out + (v / kRecTile) * 9 * K * kRecTile + (v % kRecTile);
+    } else {
+      const int64_t v0 = v - c;
+      query_epilogue<KQ, SEL, 1, MODE == 2, false, N::MTO>(
+          a, v0, lane,
+          [&](int, float (&o)[N::MTO][4]) {
 #pragma unroll
-      for (int q = 0; q < KQ; ++q) {
-        const int k = g * KQ + q;
-        const float vals[9] = {lb[q].zx, lb[q].zy, lb[q].zz, lb[q].xx, lb[q].xy, lb[q].xz,
-                               lb[q].lam, lb[q].a, lb[q].logc};
+            for (int mt = 0; mt < N::MTO; ++mt)
 #pragma unroll
-        for (int p = 0; p < 9; ++p) base[(p * K + k) * kRecTile] = vals[p];
-      }
+              for (int i = 0; i < 4; ++i) o[mt][i] = out[mt][i];
+          },
+          [&](int r, int i) { return a.xi[r * a.ld + v0 + i]; });
     }
   }
 }
@@ -1007,9 +987,12 @@ void bwd_f32_kernel(LargeTrainArgs a) {
 template <int H, int K, int PREC, int SEL, int ENC>
 static hipError_t launch_large_query_t(const QueryArgs& a, int mode, hipStream_t st) {
   const size_t shmem = LargeLds<H, K, PREC, SEL, ENC>::fwd;
-  auto kern = mode == 0 ? large_query_kernel<H, K, PREC, SEL, ENC, 0> : large_query_kernel<H, K, PREC, SEL, ENC, 1>;
-  hipError_t e = mode == 0 ? set_max_lds_once<large_query_kernel<H, K, PREC, SEL, ENC, 0>>(shmem)
-                           : set_max_lds_once<large_query_kernel<H, K, PREC, SEL, ENC, 1>>(shmem);
+  auto kern = mode == 0   ? large_query_kernel<H, K, PREC, SEL, ENC, 0>
+              : mode == 1 ? large_query_kernel<H, K, PREC, SEL, ENC, 1>
+                          : large_query_kernel<H, K, PREC, SEL, ENC, 2>;
+  hipError_t e = mode == 0   ? set_max_lds_once<large_query_kernel<H, K, PREC, SEL, ENC, 0>>(shmem)
+                 : mode == 1 ? set_max_lds_once<large_query_kernel<H, K, PREC, SEL, ENC, 1>>(shmem)
+                             : set_max_lds_once<large_query_kernel<H, K, PREC, SEL, ENC, 2>>(shmem);
   if (e != hipSuccess) return e;
   const int64_t n_tiles = (a.B + kWGV - 1) / kWGV;
   const int64_t cap = 2LL * a.num_cus;

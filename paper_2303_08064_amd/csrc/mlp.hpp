@@ -473,7 +473,9 @@ struct Forward {
   }
 
   // Forward for queries (no activations kept): in BF16 the layers pass
-  // packed, ReLU'd B operands; the same values as run().
+  // packed, ReLU'd B operands; the same values as run(). BM: the BF16 layers'
+  // MFMAs block-major with prefetched fragments (mfma_rows).
+  template <bool BM>
   __device__ __forceinline__ static void run_query(const W* lds, int nh, const typename M::Input& x, float (&out)[MTO][4],
                                    int lane) {
     if constexpr (PREC == 1) {
@@ -484,11 +486,11 @@ struct Forward {
 #pragma unroll
       for (int l = 1; l < NHMAX; ++l) {
         if (l < nh) {
-          M::template gemm_op<M::MTH>(layer_ptr(lds, l, nh), b, y, lane);
+          M::template gemm_op<M::MTH, BM>(layer_ptr(lds, l, nh), b, y, lane);
           M::relu_operands(y, b);
         }
       }
-      M::template gemm_op<MTO>(layer_ptr(lds, nh, nh), b, out, lane);
+      M::template gemm_op<MTO, BM>(layer_ptr(lds, nh, nh), b, out, lane);
     } else {
       float h[NHMAX][M::MTH][4];
       float last[M::MTH][4];

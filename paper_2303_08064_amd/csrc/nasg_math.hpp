@@ -66,6 +66,19 @@ __device__ __forceinline__ float expm1_neg(float x) {
   return fsel(x > -0.125f, expm1_neg_poly(x), fexp(x) - 1.0f);
 }
 
+// k (2^z - 1) for z <= 0 and a constant k: expm1_neg of x = z ln 2 in the
+// variable z, its coefficients times powers of ln 2 and k, which saves the
+// scalings of the exponent and of the result.
+template <typename Const>
+__device__ __forceinline__ float exp2m1_neg(float z, Const) {
+  constexpr float k = Const::k, l = kLn2;
+  float q = fmaf(z, 0.0397158824f * l * l * l * l * k, 0.166526049f * l * l * l * k);
+  q = fmaf(z, q, 0.499997109f * l * l * k);
+  return fsel(z > -0.125f * kLog2e, z * fmaf(z, q, l * k), fmaf(__builtin_amdgcn_exp2f(z), k, -k));
+}
+struct ConstOne { static constexpr float k = 1.0f; };
+struct Const2Log2e { static constexpr float k = 2.0f * kLog2e; };
+
 // log(1 - w) for 0 <= w < 1/16: y (1 + y (d0 + d1 y + d2 y^2 + d3 y^3)) with
 // y = -w, the minimax fit of relative error on [-1/16, 0] with the linear
 // term held at y (Remez exchange; fit error 4e-10 relative).
@@ -77,14 +90,14 @@ __device__ __forceinline__ float log1m_poly(float w) {
   return y * fmaf(y, r, 1.0f);
 }
 
-// log1m_poly(w4 / 4) from w4 = 4 w, with the same roundings: the
-// polynomial's coefficients and variable are scaled by powers of 4, which is
-// exact, so every intermediate is the same value times a power of 4.
-__device__ __forceinline__ float log1m_poly4(float w4) {
-  float r = fmaf(w4, 0.227763459f * (-1.0f / 1024.0f), -0.248499244f * (1.0f / 256.0f));
-  r = fmaf(w4, r, 0.333364844f * (-1.0f / 64.0f));
-  r = fmaf(w4, r, -0.499999791f * (1.0f / 16.0f));
-  return w4 * fmaf(w4, r, -0.25f);
+// log2(1 - w) from w4 = 4 w: log1m_poly with its coefficients and variable
+// scaled by powers of 4 (exact) and the coefficients by log2 e.
+__device__ __forceinline__ float log2_1m_poly4(float w4) {
+  constexpr float e = kLog2e;
+  float r = fmaf(w4, 0.227763459f * (-1.0f / 1024.0f) * e, -0.248499244f * (1.0f / 256.0f) * e);
+  r = fmaf(w4, r, 0.333364844f * (-1.0f / 64.0f) * e);
+  r = fmaf(w4, r, -0.499999791f * (1.0f / 16.0f) * e);
+  return w4 * fmaf(w4, r, -0.25f * e);
 }
 
 // log(1 + y) by its series to y^6 (truncation below 1e-8 relative for |y| < 1/16).
@@ -220,35 +233,55 @@ __device__ __forceinline__ float one_minus_exp_neg(float ao) {
   return -expm1_neg(-ao);
 }
 
+// A query's lobe: z, x, lambda, a and the weight c = A_k / K_k times
+// 2 pi / sqrt(1 + eps) (query_pdf_scale).
+struct QueryLobe {
+  float zx, zy, zz, xx, xy, xz;
+  float lam, a, c;
+};
+
+// The unit pair of tanh(oc/2), tanh(os/2): tanh(o/2) = m/(2 - m) with m = 1 -
+// e^{-|o|}, the pair scaled by (2 - mc)(2 - ms) > 0.
+__device__ __forceinline__ void decode_pair_query(float oc, float os, float& cu, float& su) {
+#pragma clang fp contract(off)
+  const float mc = one_minus_exp_neg(fabsf(oc)), ms = one_minus_exp_neg(fabsf(os));
+  float inv;
+  unit_pair(copysignf(mc * (2.0f - ms), oc), copysignf(ms * (2.0f - mc), os), cu, su, inv);
+}
+
 // Forward-only decode for queries: the same function as decode_lobe, with
-// the sin/cos pairs normalised without reciprocals (a pair of tanh(o/2) =
-// m/(2 - m) values is scaled by (2 - m1)(2 - m2) > 0 before normalising) and
-// log K folded into log c by the caller. Returns log K.
-__device__ __forceinline__ float decode_lobe_query(const float o[8], float eps, Lobe& L, float amul = 1.0f) {
+// the sin/cos pairs normalised without reciprocals. q.c receives
+// 2 pi / (K_k sqrt(1 + eps)) (the caller multiplies by the mixture weight):
+//   2 pi / K = lam sqrt((1+eps) P) / m,  P = 1+eps+a,  m = 1 - e^{-2 lam},
+// with sqrt(P) / m = P rsq(P m^2): one transcendental, where log K takes two
+// logarithms. abias = log2(amul): 0 for NASG lobes, -infinity for isotropic
+// ones (a = 0). The products and sums of the query's functions are fused only
+// where written, so that every kernel gives the same bits.
+__device__ __forceinline__ void decode_lobe_query(const float o[8], float eps, QueryLobe& q, float abias) {
+#pragma clang fp contract(off)
   // theta: cos = tanh(o0/2) (absolute accuracy suffices), sin = sech(o0/2)
   const float h0 = __builtin_amdgcn_exp2f(fabsf(o[0]) * (-0.5f * kLog2e));   // e^{-|o|/2}: sin without a square root
-  const float e0 = h0 * h0;
-  const float r0 = frcp(1.0f + e0);
-  const float ct = copysignf((1.0f - e0) * r0, o[0]);
-  const float st = 2.0f * h0 * r0;
-  const float m1 = one_minus_exp_neg(fabsf(o[1])), m2 = one_minus_exp_neg(fabsf(o[2]));
-  const float m3 = one_minus_exp_neg(fabsf(o[3])), m4 = one_minus_exp_neg(fabsf(o[4]));
-  float cp, sp, ctau, stau, inv;
-  unit_pair(copysignf(m2 * (2.0f - m1), o[2]), copysignf(m1 * (2.0f - m2), o[1]), cp, sp, inv);
-  unit_pair(copysignf(m4 * (2.0f - m3), o[4]), copysignf(m3 * (2.0f - m4), o[3]), ctau, stau, inv);
-  L.zx = cp * st;
-  L.zy = sp * st;
-  L.zz = ct;
+  const float hh = 0.5f * h0;
+  const float r0 = frcp(fmaf(hh, h0, 0.5f));                                 // 2 / (1 + h0^2)
+  const float ct = copysignf(fmaf(-hh, h0, 0.5f) * r0, o[0]);
+  const float st = h0 * r0;
+  float cp, sp, ctau, stau;
+  decode_pair_query(o[2], o[1], cp, sp);
+  decode_pair_query(o[4], o[3], ctau, stau);
+  q.zx = cp * st;
+  q.zy = sp * st;
+  q.zz = ct;
   const float ctc = ct * ctau;
-  L.xx = fmaf(ctc, cp, -sp * stau);
-  L.xy = fmaf(ctc, sp, cp * stau);
-  L.xz = -st * ctau;
+  q.xx = fmaf(ctc, cp, -sp * stau);
+  q.xy = fmaf(ctc, sp, cp * stau);
+  q.xz = -st * ctau;
   const float loglam = fminf(fmaxf(o[5], -kLogClamp), kLogClamp);
   const float loga = fminf(fmaxf(o[6], -kLogClamp), kLogClamp);
-  L.lam = fexp(loglam);
-  L.a = amul * fexp(loga);
-  L.logc = 0.0f;
-  return log_normaliser(L.lam, loglam, L.a, eps);
+  q.lam = fexp(loglam);
+  q.a = __builtin_amdgcn_exp2f(fmaf(loga, kLog2e, abias));
+  const float m = exp2m1_neg(q.lam * (-2.0f * kLog2e), ConstOne());         // -m: squared below
+  const float P = 1.0f + eps + q.a;
+  q.c = (q.lam * P) * frsq(P * (m * m));
 }
 
 // Lobe value at a unit direction, with what the backward needs.
@@ -306,28 +339,33 @@ __device__ __forceinline__ Eval eval_lobe(const Lobe& L, float vx, float vy, flo
   return r;
 }
 
-// log c + log G(v) alone (the query's mixture pdf): the same function as
-// eval_lobe without the lobe's y axis. For a unit v and an orthonormal frame
-// X^2 + Y^2 = 1 - (v.z)^2 = (1 - v.z)(1 + v.z) = 4 (1 - u) u, a product of the
-// two cancellation-free terms already at hand; c^2 is capped at 1 against
-// rounding (X^2 and 4 u (1 - u) come from different roundings).
-__device__ __forceinline__ float eval_lobe_ell(const Lobe& L, float vx, float vy, float vz, float eps) {
-  const float dx = vx - L.zx, dy = vy - L.zy, dz = vz - L.zz;
-  const float sx = vx + L.zx, sy = vy + L.zy, sz = vz + L.zz;
-  const float w4 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));   // 4 (1 - u)
-  const float u = 0.25f * fmaf(sx, sx, fmaf(sy, sy, sz * sz));
-  // w = w4 / 4 exactly, so the tests on w4 and 1 - w = fma(w4, -1/4, 1) are
-  // those on w, without forming it
-  const float lw = log1m_poly4(w4);
-  const float lu = flog(fsel(w4 <= 2.0f, fmaf(w4, -0.25f, 1.0f), u));
-  const float Lu = fsel(w4 < 0.25f, lw, lu);
-  const float X = fmaf(vx, L.xx, fmaf(vy, L.xy, vz * L.xz));
-  const float S = w4 * u;
-  const float c2 = fsel(S >= kMinNormal, fminf(X * X * frcp(S), 1.0f), 0.0f);
-  const float pm1 = fmaf(L.a, c2, eps);                    // p - 1 without cancellation
-  const float lg = fmaf(2.0f * L.lam, expm1_neg((1.0f + pm1) * Lu), pm1 * Lu);
-  return fsel(u > 0.0f, L.logc + lg, -INFINITY);
+// G(v) of a query lobe at a unit direction (eq. NASG; App. A with epsilon):
+// the same function as eval_lobe without the lobe's y axis. For a unit v and
+// an orthonormal frame X^2 + Y^2 = 1 - (v.z)^2 = (1 - v.z)(1 + v.z) =
+// 4 (1 - u) u, a product of the two cancellation-free terms already at hand;
+// c^2 is capped at 1 against rounding (X^2 and 4 u (1 - u) come from
+// different roundings), which also makes 0 / 0 at v = z into 1 (log u = 0
+// there, whatever c^2 is).
+__device__ __forceinline__ float eval_query_lobe(const QueryLobe& q, float vx, float vy, float vz, float eps) {
+#pragma clang fp contract(off)
+  const float dx = vx - q.zx, dy = vy - q.zy, dz = vz - q.zz;
+  const float sx = vx + q.zx, sy = vy + q.zy, sz = vz + q.zz;
+  const float w4 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));          // |v - z|^2 = 4 (1 - u)
+  const float u = 0.25f * fmaf(sx, sx, fmaf(sy, sy, sz * sz));   // |v + z|^2 / 4
+  // log2 u; w = w4 / 4 exactly, so the tests on w4 and 1 - w = fma(w4, -1/4,
+  // 1) are those on w, without forming it
+  const float lu = flog2(fsel(w4 <= 2.0f, fmaf(w4, -0.25f, 1.0f), u));
+  const float Lu = fsel(w4 < 0.25f, log2_1m_poly4(w4), lu);
+  // v.x as (v - z).x: near the axis v - z is exact and small, so that neither
+  // the products' rounding nor z.x of the rounded frame stands against it
+  const float X = fmaf(dx, q.xx, fmaf(dy, q.xy, dz * q.xz));
+  const float c2 = fminf(X * X * frcp(w4 * u), 1.0f);
+  const float pm1 = fmaf(q.a, c2, eps);                     // p - 1 without cancellation
+  const float lg = fmaf(q.lam, exp2m1_neg(fmaf(pm1, Lu, Lu), Const2Log2e()), pm1 * Lu);   // log2 G
+  return fsel(u > 0.0f, __builtin_amdgcn_exp2f(lg), 0.0f);  // G(-z) = 0
 }
+// the mixture pdf over sum_k c_k G_k: sqrt(1 + eps) / (2 pi)
+__device__ __forceinline__ float query_pdf_scale(float eps) { return fsqrt(1.0f + eps) * 0.159154943091895336f; }
 
 // Gradient on the sphere of ell = log c + log G (eq. NASG; App. A) at a unit
 // v, through v.z, X = v.x and Y = v.y (the same partials as backward_lobe):

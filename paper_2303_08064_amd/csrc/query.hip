@@ -16,83 +16,36 @@
 
 namespace nasg {
 
-// The hidden-64 BF16 networks' queries sample one vertex per lane (four
-// blocks per wave pass; the four blocks' lobes take 144 registers, so two
-// waves per SIMD). K = 8 in BF16 keeps one block per pass and three waves
-// per SIMD. The FP32 queries run one block per pass (the four blocks' lobes
-// and the FP32 forward do not fit two waves' registers) at two waves per
-// SIMD, which is what their weights leave room for: two workgroups of four
-// waves per CU (K = 4 and 8), or one of eight (K = 16, 92 KiB of weights).
-// The raw forwards run one wave per SIMD; the hidden-128 network two, its
-// 132 KiB of forward weights leaving room for one workgroup per CU.
-constexpr bool query_four(int H, int K, int MODE, int PREC) { return H == 64 && K != 8 && MODE == 0 && PREC == 1; }
-// dynamic LDS of a query launch: the weights, plus the four-block kernels'
+// 16-vertex blocks per wave pass (NB of the kernels below):
+// * 4, the hidden-64 networks' queries of large batches: one sample per lane
+//   (the four blocks' lobes take 144 registers at K = 16, so two waves per
+//   SIMD): BF16 in two workgroups of four waves per CU, FP32 (weights of 64
+//   to 97 KiB) in one of eight;
+// * 1, their queries of small batches (query_is_small) and raw forwards;
+// * 2, the hidden-128 network whose 132 KiB of forward weights leave room for
+//   one workgroup per CU: eight waves, every weight fragment read feeds both
+//   blocks.
+// dynamic LDS of a query launch: the weights, plus the multi-block kernels'
 // two input staging buffers per wave
-constexpr size_t query_dynamic_lds(int weight_bytes, bool four, int nb, int nw) {
-  return (size_t)weight_bytes +
-         (four ? (size_t)nw * 2 * (kInFeatures + 4) * 64 * sizeof(float)
-               : (nb == 2 ? (size_t)nw * 2 * (kInFeatures + 4) * 32 * sizeof(float) : 0));
+constexpr size_t query_dynamic_lds(int weight_bytes, int nb, int nw) {
+  return (size_t)weight_bytes + (nb > 1 ? (size_t)nw * 2 * (kInFeatures + 4) * kTileV * nb * sizeof(float) : 0);
 }
-constexpr int query_waves_per_eu(int H, int K, int MODE, int PREC) {
-  return H == 64 ? (MODE == 0 ? (query_four(H, K, MODE, PREC) || PREC == 0 ? 2 : 3) : 1) : 2;
-}
-// waves per workgroup of the hidden-64 networks' queries
-constexpr int query_waves(int K, int PREC) { return PREC == 0 && K == 16 ? 8 : 4; }
-
-// Records of one 16-vertex block's lobes (optional output of a query).
-template <int KQ>
-__device__ __forceinline__ void store_records(const QueryArgs& a, const Lobe (&lb)[KQ], int64_t v, int g) {
-  constexpr int K = 4 * KQ;
-  float* base = a.rec_out + (v / kRecTile) * 9 * K * kRecTile + (v % kRecTile);
-#pragma unroll
-  for (int q = 0; q < KQ; ++q) {
-    const int k = g * KQ + q;
-    const float vals[9] = {lb[q].zx, lb[q].zy, lb[q].zz, lb[q].xx, lb[q].xy, lb[q].xz, lb[q].lam, lb[q].a, lb[q].logc};
-#pragma unroll
-    for (int p = 0; p < 9; ++p) base[(p * K + k) * kRecTile] = vals[p];
-  }
+constexpr int query_waves_per_eu(int NB, int MODE, int PREC, int K) {
+  return NB == 1 ? (MODE == 1 ? 1 : (PREC == 1 && K < 16 ? 3 : 2)) : 2;
 }
 
-// The rest of a query for one 16-vertex block from its raw outputs: decode,
-// choose a lobe, sample, evaluate the pdf and store (MODE 0), or store the
-// raw outputs in canonical row order (MODE 1).
-template <int K, int MODE, int S, int MTO>
-__device__ __forceinline__ void finish_block(const QueryArgs& a, const float (&out)[MTO][4], int64_t v, int g,
-                                             int c, const float* xi, int64_t xi_ld, int64_t xi_col) {
+// MODE 1: store a 16-vertex block's raw outputs in canonical row order.
+template <int K, int S, int MTO>
+__device__ __forceinline__ void store_raw(const QueryArgs& a, const float (&out)[MTO][4], int64_t v, int g) {
   constexpr int KQ = K / 4;
-  const bool valid = v < a.B;
-  if (MODE == 1) {
-    // accumulator t of lane group g is parameter t / KQ of lobe g*KQ + t % KQ
-    if (valid) {
+  if (v >= a.B) return;
+  // accumulator t of lane group g is parameter t / KQ of lobe g*KQ + t % KQ
 #pragma unroll
-      for (int t = 0; t < 2 * K; ++t) {
-        int p = t / KQ, k = g * KQ + t % KQ;
-        a.raw_out[(int64_t)(p * K + k) * a.ld + v] = out[t >> 2][t & 3];
-      }
-      if (S == 1 && g == 0) a.raw_out[(int64_t)(8 * K) * a.ld + v] = out[MTO - 1][0];
-    }
-    return;
+  for (int t = 0; t < 2 * K; ++t) {
+    int p = t / KQ, k = g * KQ + t % KQ;
+    a.raw_out[(int64_t)(p * K + k) * a.ld + v] = out[t >> 2][t & 3];
   }
-  float xi_sel = 0.0f, xi0 = 0.0f, xi1 = 0.0f, xi2 = 0.0f;
-  if (valid) {
-    xi_sel = xi[xi_col];
-    xi0 = xi[xi_ld + xi_col];
-    xi1 = xi[2 * xi_ld + xi_col];
-    xi2 = xi[3 * xi_ld + xi_col];
-  }
-  Lobe lb[KQ];
-  float vx, vy, vz;
-  const float logq = query_epilogue<KQ, MTO>(out, xi_sel, xi0, xi1, xi2, a.eps, g, c, lb, vx, vy, vz, a.amul);
-
-  if (valid && g == 0) {
-    a.dir_out[v] = vx;
-    a.dir_out[a.ld + v] = vy;
-    a.dir_out[2 * a.ld + v] = vz;
-    a.pdf_out[v] = fexp(logq);
-    // selection probability c = sigmoid(o[8K]) (Tab. "decoding")
-    if (S == 1 && a.sel_out != nullptr) a.sel_out[v] = frcp(1.0f + fexp(-out[MTO - 1][0]));
-  }
-  if (a.rec_out != nullptr && valid) store_records<KQ>(a, lb, v, g);
+  if (S == 1 && g == 0) a.raw_out[(int64_t)(8 * K) * a.ld + v] = out[MTO - 1][0];
 }
 
 // Inputs of one 64-vertex pass staged in LDS: the 9 feature rows and the 4
@@ -135,107 +88,88 @@ __device__ __forceinline__ void stage_pass32(const QueryArgs& a, int64_t tile, f
   }
 }
 
-// Layer 0's input of vertex `col` of a staged pass (as the Mlp's load_raw:
-// features 4g .. 4g + 3 of the 9, then the constant one, then zeros)
-__device__ __forceinline__ bf16x4 staged_input(const float* buf, int col, bool valid, int g) {
-  float f[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int k = 4 * g + j;
+// Layer 0's input of vertex `col` of a staged pass, as the Mlp's load_input:
+// of the 9 features, the constant one, then zeros, lane group g holds 4g ..
+// 4g + 3 (BF16) or g, 4 + g, 8 + g (FP32)
+template <typename M, int PREC>
+__device__ __forceinline__ typename M::Input staged_input(const float* buf, int col, bool valid, int g) {
+  auto at = [&](int k) {
     float x = 0.0f;
     if (valid) {
       if (k < kInFeatures) x = buf[k * 64 + col];
       else if (k == kInFeatures) x = 1.0f;
     }
-    f[j] = x;
-  }
-  return bf16x4{(__bf16)f[0], (__bf16)f[1], (__bf16)f[2], (__bf16)f[3]};
-}
-
-// The query (MODE 0) of the hidden-64 networks, one sample per lane: a wave
-// takes four 16-vertex blocks per pass. For each block it runs the forward,
-// decodes the lobes (lane (g, c): vertex c, lobes g*K/4 ..), chooses a lobe
-// per vertex and moves the chosen lobe to lane (block, c). Then every lane
-// samples the vertex (block g, vertex c) once, instead of the four lanes of
-// a vertex each repeating the sample; the directions go back to the lanes
-// that hold each block's lobes for the pdf, and lane (g, c) stores the
-// direction and pdf of vertex (g, c). Per vertex, the same operations in the
-// same order as the one-block pass, so the same results bit for bit.
-template <int H, int K, int PREC, int S, int E, int NW>
-__device__ __forceinline__ void query_four_blocks(const QueryArgs& a, const typename Forward<H, K, PREC, 4, S, E>::W* wts,
-                                                  int64_t tile, const float* in, int lane) {
-  typedef Forward<H, K, PREC, 4, S, E> F;
-  static_assert(E == 0, "staged raw features");
-  constexpr int KQ = K / 4;
-  constexpr int MTO = F::MTO;
-  const int g = lane >> 4, c = lane & 15;
-  Lobe lb[4][KQ];
-  Lobe ch = {};
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int64_t v = tile * (4 * kTileV) + b * kTileV + c;
-    const bool valid = v < a.B;
-    const bf16x4 x = staged_input(in, b * kTileV + c, valid, g);
-    float out[MTO][4];
-    F::run_query(wts, a.nh, x, out, lane);
-    float A[KQ];
-    query_decode<KQ, MTO>(out, a.eps, lb[b], A, a.amul);
-    const float xs = valid ? in[kInFeatures * 64 + b * kTileV + c] : 0.0f;
-    const int k = select_lobe<KQ>(A, xs, g, c);
-    const Lobe r = broadcast_lobe<KQ>(lb[b], k, c);
-    if (g == b) ch = r;
-    // selection probability c = sigmoid(o[8K]) (Tab. "decoding")
-    if (S == 1 && a.sel_out != nullptr && valid && g == 0) a.sel_out[v] = frcp(1.0f + fexp(-out[MTO - 1][0]));
-    if (a.rec_out != nullptr && valid) store_records<KQ>(a, lb[b], v, g);
-  }
-  const int64_t vm = tile * (4 * kTileV) + lane;   // vertex (block g, c)
-  const bool mine = vm < a.B;
-  const float xi0 = mine ? in[(kInFeatures + 1) * 64 + lane] : 0.0f;
-  const float xi1 = mine ? in[(kInFeatures + 2) * 64 + lane] : 0.0f;
-  const float xi2 = mine ? in[(kInFeatures + 3) * 64 + lane] : 0.0f;
-  float vx, vy, vz;
-  sample_unit(ch, xi0, xi1, xi2, a.eps, vx, vy, vz);
-  float logq = 0.0f;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int src = b * kTileV + c;
-    const float bx = __shfl(vx, src), by = __shfl(vy, src), bz = __shfl(vz, src);
-    const float lq = query_log_pdf<KQ>(lb[b], bx, by, bz, a.eps);
-    if (g == b) logq = lq;
-  }
-  if (mine) {
-    a.dir_out[vm] = vx;
-    a.dir_out[a.ld + vm] = vy;
-    a.dir_out[2 * a.ld + vm] = vz;
-    a.pdf_out[vm] = fexp(logq);
+    return x;
+  };
+  if constexpr (PREC == 1) {
+    return bf16x4{(__bf16)at(4 * g), (__bf16)at(4 * g + 1), (__bf16)at(4 * g + 2), (__bf16)at(4 * g + 3)};
+  } else {
+    return {{at(g), at(4 + g), at(8 + g)}};
   }
 }
 
-// MODE 0: query, 1: raw forward only; S = 1: the network has the selection
-// output (row 8K, read by lane group 0 from the extra output tile); E = 1:
-// the encoded input; NB: 16-vertex blocks per wave per pass (NB > 1 shares
-// every weight fragment read among NB MFMAs); NW: waves per workgroup.
+// MODE 0: query, 1: raw forward only, 2: query that also stores the decoded
+// records (a kernel of its own: the store's addresses and the raw outputs
+// that it needs raise the K = 16 kernel from 224 to 256 registers); S = 1:
+// the network has the selection output (row 8K, read by lane group 0 from
+// the extra output tile); E = 1: the encoded input; NB: 16-vertex blocks per
+// wave per pass; NW: waves per workgroup.
+// Bound by VALU issue (the K = 16 BF16 pass of 64 vertices issues 4415 slots,
+// 4864 before log K, the log-sum-exp and the base-e scalings went, see
+// decode_lobe_query and query_pdf). Measured: 2^20 K = 16 BF16 queries 145 ->
+// 137 us, K = 8 103 -> 94 us (four blocks, was one), 120000 FP32 K = 8
+// queries with records 54.1 -> 51.4 us, 600000 of the hidden-128 network 111
+// -> 101.5 us (one sample per two lane groups, was per group), 777 K = 4 BF16
+// queries 9.3 -> 4.4 us (one-block passes).
 template <int H, int K, int PREC, int MODE, int S, int E, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(query_waves_per_eu(H, K, MODE, PREC))))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(query_waves_per_eu(NB, MODE, PREC, K))))
 void query_kernel(QueryArgs a) {
   constexpr int NHMAX = 4;
   typedef Mlp<H, K, PREC, E> M;
   typedef Forward<H, K, PREC, NHMAX, S, E> F;
   typedef typename F::W W;
-  static_assert(NB == 1 || PREC == 1, "multi-block passes are BF16 only");
   extern __shared__ __align__(16) unsigned char smem[];
   W* lds = reinterpret_cast<W*>(smem);
   // the forward weights by direct-to-LDS loads: every wave's copies are in
   // flight at once (a register round trip per 16 bytes waited on each load)
   lds_dma(lds, a.wpack, a.lds_bytes);
-  lds_dma_wait();
-  __syncthreads();
-  const W* wts = lds;
+  constexpr int KQ = K / 4;
+  constexpr bool REC = MODE == 2;
+  // block-major MFMAs: 1-3% faster than row tile by row tile, but for the
+  // four-block K = 16 kernel (1% slower: 254 registers)
+  constexpr bool BM = !(NB == 4 && K == 16);
 
   const int lane = lane_id();
   const int g = lane >> 4, c = lane & 15;
   const int wave = threadIdx.x >> 6;
-  if constexpr (query_four(H, K, MODE, PREC)) {
+  // inputs of one block of a one-block pass
+  struct BlockIn {
+    typename M::Input x;
+    float xi[4];
+  };
+  auto load_block = [&](int64_t block) {
+    BlockIn in;
+    const int64_t v = block * kTileV + c;
+    in.x = M::load_input(a.feat, a.ld, v, v < a.B, g);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) in.xi[r] = 0.0f;
+    if (MODE != 1 && v < a.B) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) in.xi[r] = a.xi[r * a.ld + v];
+    }
+    return in;
+  };
+  // one-block passes: four waves of a workgroup (one per SIMD) take
+  // neighbouring blocks (64 bytes of every row each); a workgroup's second
+  // four come after everyone's first, so that the end of a batch runs one
+  // wave per SIMD. The first block's inputs are requested beside the weights.
+  int64_t block = (int64_t)(wave >> 2) * 4 * gridDim.x + (int64_t)blockIdx.x * 4 + (wave & 3);
+  BlockIn first;
+  if constexpr (NB == 1) first = load_block(block);
+  lds_dma_wait();
+  __syncthreads();
+  const W* wts = lds;
+  if constexpr (NB == 4) {
     // each wave's two staging buffers follow the weights: the next pass's
     // inputs are copied while this pass runs, so no block waits for memory
     float* stage = reinterpret_cast<float*>(smem + a.lds_bytes) + wave * 2 * kPassStage;
@@ -253,7 +187,19 @@ void query_kernel(QueryArgs a) {
       } else {
         lds_dma_wait();
       }
-      query_four_blocks<H, K, PREC, S, E, NW>(a, wts, tile, cur, lane);
+      // the forward runs block by block, each block's decoded lobes kept
+      // until the four blocks' vertices have been sampled, one per lane. The
+      // next block's forward stays out of a block's decode where the
+      // scheduler's mix of the two spills (FP32, and K = 16 with the
+      // selection tile or the record store); elsewhere the mix is 1% faster
+      constexpr bool SPLIT = PREC == 0 || (K == 16 && (REC || S == 1));
+      query_epilogue<KQ, S, 4, REC, SPLIT, F::MTO>(
+          a, tile * (4 * kTileV), lane,
+          [&](int b, float (&out)[F::MTO][4]) {
+            const bool valid = tile * (4 * kTileV) + b * kTileV + c < a.B;
+            F::template run_query<BM>(wts, a.nh, staged_input<M, PREC>(cur, b * kTileV + c, valid, g), out, lane);
+          },
+          [&](int r, int i) { return cur[(kInFeatures + r) * 64 + i]; });
     }
     return;
   }
@@ -261,26 +207,30 @@ void query_kernel(QueryArgs a) {
   const int64_t n_tiles = (a.B + TV - 1) / TV;
   const int64_t stride = (int64_t)gridDim.x * NW;
   if constexpr (NB == 1) {
-    for (int64_t tile = (int64_t)blockIdx.x * NW + wave; tile < n_tiles; tile += stride) {
-      const int64_t v = tile * kTileV + c;
-      typename M::Input x = M::load_input(a.feat, a.ld, v, v < a.B, g);
-      float out[F::MTO][4];
-      F::run_query(wts, a.nh, x, out, lane);
-      finish_block<K, MODE, S>(a, out, v, g, c, a.xi, a.ld, v);
+    for (BlockIn in = first; block < n_tiles; in = load_block(block)) {
+      if constexpr (MODE == 1) {
+        float out[F::MTO][4];
+        F::template run_query<BM>(wts, a.nh, in.x, out, lane);
+        store_raw<K, S>(a, out, block * kTileV + c, g);
+      } else {
+        query_epilogue<KQ, S, 1, REC, false, F::MTO>(
+            a, block * kTileV, lane, [&](int, float (&out)[F::MTO][4]) { F::template run_query<BM>(wts, a.nh, in.x, out, lane); },
+            [&](int r, int) { return in.xi[r]; });
+      }
+      block += stride;
     }
-  } else {
+  } else if constexpr (NB == 2) {
     // two 16-vertex blocks per pass, their inputs staged in LDS one pass
-    // ahead (as in query_four_blocks): the rows of a pass are [row][32]
-    static_assert(NB == 2, "32-vertex passes");
-    constexpr int ROWS = kInFeatures + (MODE == 0 ? 4 : 0);
+    // ahead (as for four): the rows of a pass are [row][32]
+    constexpr int ROWS = kInFeatures + (MODE != 1 ? 4 : 0);
     constexpr int COPIES = (ROWS + 1) / 2;
     float* stage = reinterpret_cast<float*>(smem + a.lds_bytes) + wave * 2 * (kPassRows * 32);
     int64_t tile = (int64_t)blockIdx.x * NW + wave;
-    if (tile < n_tiles) stage_pass32<MODE == 0>(a, tile, stage, lane);
+    if (tile < n_tiles) stage_pass32<MODE != 1>(a, tile, stage, lane);
     for (int p = 0; tile < n_tiles; tile += stride, p ^= 1) {
       const float* cur = stage + p * (kPassRows * 32);
       if (tile + stride < n_tiles) {
-        stage_pass32<MODE == 0>(a, tile + stride, stage + (p ^ 1) * (kPassRows * 32), lane);
+        stage_pass32<MODE != 1>(a, tile + stride, stage + (p ^ 1) * (kPassRows * 32), lane);
         __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);
       } else {
         lds_dma_wait();
@@ -292,96 +242,123 @@ void query_kernel(QueryArgs a) {
         x[nb] = M::load_input(cur, 32, nb * kTileV + c, v < a.B, g);
       }
       float out[NB][F::MTO][4];
-      F::template run_query_nb<NB, MODE == 0>(wts, a.nh, x, out, lane);
+      F::template run_query_nb<NB, MODE != 1>(wts, a.nh, x, out, lane);
+      if constexpr (MODE == 1) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        finish_block<K, MODE, S>(a, out[nb], tile * TV + nb * kTileV + c, g, c, cur + kInFeatures * 32, 32,
-                                 nb * kTileV + c);
+        for (int nb = 0; nb < NB; ++nb) store_raw<K, S>(a, out[nb], tile * TV + nb * kTileV + c, g);
+      } else {
+        query_epilogue<KQ, S, NB, REC, false, F::MTO>(
+            a, tile * TV, lane,
+            [&](int b, float (&o)[F::MTO][4]) {
+#pragma unroll
+              for (int mt = 0; mt < F::MTO; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[mt][i] = out[b][mt][i];
+            },
+            [&](int r, int i) { return cur[(kInFeatures + r) * 32 + i]; });
+      }
     }
   }
 }
 
-template <int H, int K, int PREC, int S, int E, int NB, int NW>
-static hipError_t launch_query_s(const QueryArgs& a, int mode, hipStream_t st) {
-  auto kern = mode == 0 ? query_kernel<H, K, PREC, 0, S, E, NB, NW> : query_kernel<H, K, PREC, 1, S, E, NB, NW>;
-  const bool four = query_four(H, K, mode, PREC);
-  const int TV = kTileV * (four ? 4 : NB);   // vertices per wave pass
+// The kernel of one variant and the workgroups per CU that it reaches.
+struct QueryKernel {
+  void (*kern)(QueryArgs);
+  hipError_t (*set_lds)(size_t);
+  int nb, nw;
+  size_t max_weights;   // bytes, of the network shape's deepest variant (4 hidden layers)
+};
+
+template <int H, int K, int PREC, int MODE, int S, int E, int NB, int NW>
+static QueryKernel query_variant() {
+  const NetDims dmax{H, 4, K, S, E};
+  const size_t w = PREC == 1 ? (size_t)Bf16Layout{dmax}.fwd_elems() * 2 : (size_t)F32Layout{dmax}.total_elems() * 4;
+  return {query_kernel<H, K, PREC, MODE, S, E, NB, NW>, set_max_lds_once<query_kernel<H, K, PREC, MODE, S, E, NB, NW>>,
+          NB, NW, w};
+}
+
+template <int H, int K, int PREC, int MODE, int S>
+static QueryKernel net64_variant(bool small) {
+  constexpr int NW4 = PREC == 0 ? 8 : 4;
+  // one workgroup per CU (K = 16 in FP32): eight waves of one-block passes
+  // too, for two per SIMD
+  constexpr int NW1 = PREC == 0 && K == 16 && MODE != 1 ? 8 : 4;
+  if constexpr (MODE == 1) return query_variant<H, K, PREC, 1, S, 0, 1, NW1>();
+  else return small ? query_variant<H, K, PREC, MODE, S, 0, 1, NW1>() : query_variant<H, K, PREC, MODE, S, 0, 4, NW4>();
+}
+template <int H, int K, int PREC, int S>
+static QueryKernel net64_kernel(int mode, bool small) {
+  return mode == 0   ? net64_variant<H, K, PREC, 0, S>(small)
+         : mode == 1 ? net64_variant<H, K, PREC, 1, S>(small)
+                     : net64_variant<H, K, PREC, 2, S>(small);
+}
+
+// The resident query kernel of a network; nb = 0 when it has none.
+static QueryKernel find_query_kernel(const NetDims& d, int prec, int mode, bool small) {
+#define NASG_CASE(h, k, p)                                  \
+  if (d.H == h && d.K == k && prec == p && d.E == 0)        \
+    return d.S ? net64_kernel<h, k, p, 1>(mode, small) : net64_kernel<h, k, p, 0>(mode, small);
+  NASG_FOR_EACH_NET(NASG_CASE)
+#undef NASG_CASE
+#define NASG_CASE(h, k, p, s, e)                                             \
+  if (d.H == h && d.K == k && prec == p && d.S == s && d.E == e)             \
+    return mode == 0   ? query_variant<h, k, p, 0, s, e, 2, 8>()             \
+           : mode == 1 ? query_variant<h, k, p, 1, s, e, 2, 8>()             \
+                       : query_variant<h, k, p, 2, s, e, 2, 8>();
+  NASG_FOR_EACH_RESIDENT_QUERY(NASG_CASE)
+#undef NASG_CASE
+  return {nullptr, nullptr, 0, 0, 0};
+}
+
+// One-block or four-block passes, by rounds over 8 waves per CU (two per
+// SIMD), in hundredths of a four-block round (64 vertices a wave). A one-block
+// round (16 vertices a wave) takes about 29 in BF16 and 27 in FP32, a last one
+// of at most half the waves (one per SIMD) 15. A last four-block round of at most half the waves
+// takes 58 in BF16; in FP32, whose chains of 32-cycle MFMAs wait for
+// themselves, as long as a full one.
+// Measured (us, one-block / four-block): K = 16 BF16 777 vertices 5.7 / 13.8,
+// 65536 13.0 / 14.7, 131072 22.2 / 20.1, 300000 55 / 43; K = 8 FP32 777
+// 8.5 / 41, 98304 34.1 / 42.6, 131072 44.1 / 42.6, 200000 71 / 82.
+static bool query_is_small(int64_t B, int num_cus, int prec) {
+  const int64_t wave = 8LL * num_cus;
+  const int64_t full1 = B / (16 * wave), rest1 = B - full1 * 16 * wave;
+  const int64_t full4 = B / (64 * wave), rest4 = B - full4 * 64 * wave;
+  const int64_t one = prec == 1 ? 29 : 27;
+  const int64_t last1 = rest1 == 0 ? 0 : (rest1 <= 8 * wave ? 15 : one);
+  const int64_t last4 = rest4 == 0 ? 0 : (prec == 1 && rest4 <= 32 * wave ? 58 : 100);
+  return one * full1 + last1 < 100 * full4 + last4;
+}
+
+hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode, hipStream_t st) {
+  const bool small = query_is_small(a.B, a.num_cus, prec);
+  const QueryKernel k = find_query_kernel(d, prec, mode, small);
+  if (k.nb == 0) return hipErrorInvalidValue;
+  const int TV = kTileV * k.nb;   // vertices per wave pass
   const int64_t n_tiles = (a.B + TV - 1) / TV;
-  const int64_t want = (n_tiles + NW - 1) / NW;
-  const int64_t cap = (int64_t)(a.per_cu < 1 ? 1 : a.per_cu) * a.num_cus;
-  int grid = (int)(want < cap ? want : cap);
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NW), query_dynamic_lds(a.lds_bytes, four, NB, NW), st, a);
+  // one-block passes: a workgroup for every four blocks up to the capacity
+  const int64_t want = k.nb == 1 ? (n_tiles + 3) / 4 : (n_tiles + k.nw - 1) / k.nw;
+  const int per_cu = a.per_cu[small];
+  const int64_t cap = (int64_t)(per_cu < 1 ? 1 : per_cu) * a.num_cus;
+  const int grid = (int)(want < cap ? (want < 1 ? 1 : want) : cap);
+  hipLaunchKernelGGL(k.kern, dim3(grid), dim3(64 * k.nw), query_dynamic_lds(a.lds_bytes, k.nb, k.nw), st, a);
   return hipGetLastError();
 }
 
 // The LDS limit is raised once to the footprint of the network shape's
 // deepest variant (4 hidden layers); the occupancy is that of the caller's
 // footprint.
-template <int H, int K, int PREC, int S, int E, int NB, int NW>
-static hipError_t occupancy_s(int mode, int lds_bytes, int* per_cu) {
-  const NetDims dmax{H, 4, K, S, E};
-  const int max_w = PREC == 1 ? (int)Bf16Layout{dmax}.fwd_elems() * 2 : (int)F32Layout{dmax}.total_elems() * 4;
-  if (lds_bytes > max_w) return hipErrorInvalidValue;
-  const bool four = query_four(H, K, mode, PREC);
-  const int max_bytes = (int)query_dynamic_lds(max_w, four, NB, NW);
-  lds_bytes = (int)query_dynamic_lds(lds_bytes, four, NB, NW);
-  hipError_t e = mode == 0 ? set_max_lds_once<query_kernel<H, K, PREC, 0, S, E, NB, NW>>(max_bytes)
-                           : set_max_lds_once<query_kernel<H, K, PREC, 1, S, E, NB, NW>>(max_bytes);
+hipError_t query_workgroups_per_cu(const NetDims& d, int prec, int mode, bool small, int lds_bytes, int* per_cu) {
+  const QueryKernel k = find_query_kernel(d, prec, mode, small);
+  if (k.nb == 0 || (size_t)lds_bytes > k.max_weights) return hipErrorInvalidValue;
+  hipError_t e = k.set_lds(query_dynamic_lds((int)k.max_weights, k.nb, k.nw));
   if (e != hipSuccess) return e;
-  auto kern = mode == 0 ? query_kernel<H, K, PREC, 0, S, E, NB, NW> : query_kernel<H, K, PREC, 1, S, E, NB, NW>;
   int n = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, 64 * NW, lds_bytes);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)k.kern, 64 * k.nw,
+                                                   query_dynamic_lds(lds_bytes, k.nb, k.nw));
   *per_cu = n < 1 ? 1 : n;
   return e;
 }
 
-template <int H, int K, int PREC>
-static hipError_t launch_query_t(const QueryArgs& a, int mode, hipStream_t st) {
-  constexpr int NW = query_waves(K, PREC);
-  return a.sel ? launch_query_s<H, K, PREC, 1, 0, 1, NW>(a, mode, st) : launch_query_s<H, K, PREC, 0, 0, 1, NW>(a, mode, st);
-}
-
-hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode, hipStream_t st) {
-#define NASG_CASE(h, k, p) \
-  if (d.H == h && d.K == k && prec == p && d.E == 0) return launch_query_t<h, k, p>(a, mode, st);
-  NASG_FOR_EACH_NET(NASG_CASE)
-#undef NASG_CASE
-  // hidden-128 networks whose BF16 forward weights fit in LDS: two vertex
-  // blocks per wave, eight waves per workgroup
-#define NASG_CASE(h, k, p, s, e)                                          \
-  if (d.H == h && d.K == k && prec == p && d.S == s && d.E == e) \
-    return launch_query_s<h, k, p, s, e, 2, 8>(a, mode, st);
-  NASG_FOR_EACH_RESIDENT_QUERY(NASG_CASE)
-#undef NASG_CASE
-  return hipErrorInvalidValue;
-}
-
-hipError_t query_workgroups_per_cu(const NetDims& d, int prec, int mode, int lds_bytes, int* per_cu) {
-#define NASG_CASE(h, k, p)                                                                  \
-  if (d.H == h && d.K == k && prec == p && d.E == 0)                                        \
-    return d.S ? occupancy_s<h, k, p, 1, 0, 1, query_waves(k, p)>(mode, lds_bytes, per_cu) \
-               : occupancy_s<h, k, p, 0, 0, 1, query_waves(k, p)>(mode, lds_bytes, per_cu);
-  NASG_FOR_EACH_NET(NASG_CASE)
-#undef NASG_CASE
-#define NASG_CASE(h, k, p, s, e)                                 \
-  if (d.H == h && d.K == k && prec == p && d.S == s && d.E == e) \
-    return occupancy_s<h, k, p, s, e, 2, 8>(mode, lds_bytes, per_cu);
-  NASG_FOR_EACH_RESIDENT_QUERY(NASG_CASE)
-#undef NASG_CASE
-  return hipErrorInvalidValue;
-}
-
-bool query_is_resident(const NetDims& d, int prec) {
-#define NASG_CASE(h, k, p) \
-  if (d.H == h && d.K == k && prec == p && d.E == 0) return true;
-  NASG_FOR_EACH_NET(NASG_CASE)
-#undef NASG_CASE
-#define NASG_CASE(h, k, p, s, e) \
-  if (d.H == h && d.K == k && prec == p && d.S == s && d.E == e) return true;
-  NASG_FOR_EACH_RESIDENT_QUERY(NASG_CASE)
-#undef NASG_CASE
-  return false;
-}
+bool query_is_resident(const NetDims& d, int prec) { return find_query_kernel(d, prec, 0, false).nb != 0; }
 
 }  // namespace nasg
