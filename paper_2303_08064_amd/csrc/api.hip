@@ -409,7 +409,7 @@ static nasg_status loss_grad(nasg_ctx* ctx, const char* fn, const float* feat, c
   const nasg_state& s = ctx->st;
   const bool large = is_large(&ctx->cfg);
   const int n_wg = large ? large_train_workgroups(B, ctx->num_cus, ctx->cfg.precision)
-                         : train_workgroups(B, ctx->num_cus);
+                         : small_train_workgroups(B, ctx->num_cus, ctx->d.K, ctx->cfg.precision);
   const int n_loss = large ? large_loss_workgroups(B, ctx->num_cus, ctx->cfg.precision) : n_wg;
   TrainArgs t;
   t.wpack = s.wpack;

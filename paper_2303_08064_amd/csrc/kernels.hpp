@@ -227,6 +227,8 @@ hipError_t launch_fill(void* p, int64_t n_words, uint32_t value, hipStream_t st)
 // Query / train kernel grid bounds (workgroups) for a batch of B vertices.
 constexpr int kMaxTrainWG = 256;
 int train_workgroups(int64_t B, int num_cus);
+// the hidden-64 training kernel's grid (64- or 128-vertex tiles by the batch's size)
+int small_train_workgroups(int64_t B, int num_cus, int K, int prec);
 // the large network's training: its backward kernels' grid, the loss
 // partials it writes (the workgroups of the kernel that evaluates the loss),
 // and the bytes of its raw-output gradient images for up to B vertices

@@ -3,7 +3,7 @@
 // reduction of per-workgroup weight gradients and a fused Adam update.
 //
 // Work split of the fused kernel (one persistent workgroup per CU; eight waves
-// over 128-vertex tiles in BF16, four over 64 in FP32): each wave runs
+// over 128-vertex tiles, or four over 64: train_is_wide): each wave runs
 // forward, NASG backward and dgrad for its own 16 vertices with activations
 // in registers (nothing is written to HBM); for the weight gradient
 // dW_l = sum_v delta_l(v) h_{l-1}(v)^T the waves stage delta_l and h_{l-1}
@@ -20,11 +20,8 @@
 namespace nasg {
 
 
-// waves per training workgroup (see TrainCfg)
-template <int PREC>
-constexpr int train_waves() { return PREC == 1 ? 8 : 4; }
-
-template <int H, int K, int PREC, int SEL>
+// NW: waves per workgroup (four or eight, train_is_wide)
+template <int H, int K, int PREC, int SEL, int NW_>
 struct TrainCfg {
   typedef Mlp<H, K, PREC> M;
   typedef typename std::conditional<PREC == 1, __bf16, float>::type S;   // staging type
@@ -33,9 +30,7 @@ struct TrainCfg {
   static constexpr int MTH = H / 16;
   static constexpr int MTO = K / 2 + SEL;       // output row tiles (+ the selection tile)
   static constexpr int CTH = H / 16;            // column tiles of dW (hidden input)
-  // BF16: eight waves (two per SIMD) over 128-vertex tiles; FP32 (larger
-  // weights and staging): four waves over 64-vertex tiles
-  static constexpr int NW = train_waves<PREC>();
+  static constexpr int NW = NW_;
   static constexpr int NV = 16 * NW;            // vertices per tile
   static constexpr int RMAX = (16 * MTO > H) ? 16 * MTO : H;   // rows of the largest delta
   // staging pitch (elements). BF16: a row of NV + 16 = 144 values is 18
@@ -44,8 +39,9 @@ struct TrainCfg {
   // 2 mod 4 (measured on gfx950: 136, 152, 160, 168 and 184 values per row
   // each cost ~3 conflict cycles per read, 144 and 176 none). The selection
   // networks' staging at 144 would exceed the LDS beside their weights, so
-  // they keep 136. FP32 reads one value per lane, conflict-free at NV + 4.
-  static constexpr int SP = PREC == 1 ? (SEL == 1 ? NV + 8 : NV + 16) : NV + 4;
+  // they keep 136 (80 with four waves is free too). FP32: conflict-free at NV
+  // + 4 (a row's 16-byte units 1 mod 16, so 16 rows cover the banks).
+  static constexpr int SP = PREC == 1 ? (SEL == 1 && NW == 8 ? NV + 8 : NV + 16) : NV + 4;
   typedef Own<MTH, 1, NW> O0;                   // layer 0
   typedef Own<MTH, CTH, NW> OH;                 // hidden layers
   typedef Own<MTO, CTH, NW> OO;                 // output layer
@@ -76,11 +72,10 @@ struct TrainLds {
 
 // SEL = 1: the network has the selection output and the loss is the blend
 // of Sec. 4.2 (the BSDF pdf at each training direction is an input)
-template <int H, int K, int PREC, int SEL>
-__global__ __launch_bounds__(64 * train_waves<PREC>())
-__attribute__((amdgpu_waves_per_eu(train_waves<PREC>() / 4, train_waves<PREC>() / 4)))
+template <int H, int K, int PREC, int SEL, int NW_>
+__global__ __launch_bounds__(64 * NW_) __attribute__((amdgpu_waves_per_eu(NW_ / 4, NW_ / 4)))
 void train_kernel(TrainArgs a) {
-  typedef TrainCfg<H, K, PREC, SEL> C;
+  typedef TrainCfg<H, K, PREC, SEL, NW_> C;
   typedef typename C::M M;
   typedef typename C::S S;
   typedef TrainLds<H, K, PREC, SEL> TL;
@@ -95,8 +90,6 @@ void train_kernel(TrainArgs a) {
   S* dstB = C::RMAX >= 2 * H ? dst + H * SP : hst + H * SP;
   S* hstB = C::RMAX >= 2 * H ? hst + H * SP : dstB + H * SP;
   lds_dma(lds, a.wpack, a.lds_bytes);
-  lds_dma_wait();
-  __syncthreads();
 
   const int lane = lane_id();
   const int g = lane >> 4, c = lane & 15;
@@ -137,7 +130,9 @@ void train_kernel(TrainArgs a) {
     }
     return r;
   };
-  In nxt = load_in((int64_t)blockIdx.x * NV + wave * 16 + c);
+  In nxt = load_in((int64_t)blockIdx.x * NV + wave * 16 + c);   // in flight beside the weights
+  lds_dma_wait();
+  __syncthreads();
   for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const int64_t v = tile * NV + wave * 16 + c;
     const bool valid = v < a.B;
@@ -272,29 +267,51 @@ int train_workgroups(int64_t B, int num_cus) {
   return (int)(t < cap ? (t < 1 ? 1 : t) : cap);
 }
 
-template <int H, int K, int PREC, int SEL>
+// Eight waves over 128-vertex tiles (two waves per SIMD, so that one's LDS
+// round trips, barriers and NASG epilogue overlap the other's MFMAs) once
+// 64-vertex tiles would fill every CU, four over 64 below (twice the CUs, one
+// wave per SIMD). FP32 with K = 16: always four (its weights and the staging
+// of 128 vertices exceed the LDS). Measured (us per step, four / eight waves):
+// see train_kernel's figures beside launch_train.
+static bool train_is_wide(int64_t B, int num_cus, int K, int prec) {
+  return (prec == 1 || K < 16) && (B + kWGV - 1) / kWGV > num_cus;
+}
+
+int small_train_workgroups(int64_t B, int num_cus, int K, int prec) {
+  return train_workgroups(train_is_wide(B, num_cus, K, prec) ? (B + 1) / 2 : B, num_cus);
+}
+
+template <int H, int K, int PREC, int SEL, int NW>
 static hipError_t launch_train_s(const TrainArgs& a, int n_wg, hipStream_t st) {
-  typedef TrainCfg<H, K, PREC, SEL> C;
+  typedef TrainCfg<H, K, PREC, SEL, NW> C;
   const size_t stage = sizeof(typename C::S) * C::stage_elems();
   const size_t shmem = (size_t)a.lds_bytes + stage;
-  auto kern = train_kernel<H, K, PREC, SEL>;
+  auto kern = train_kernel<H, K, PREC, SEL, NW>;
   // the largest footprint of this network shape (4 hidden layers)
   const NetDims d{H, C::NHMAX, K, SEL};
   const size_t wmax = PREC == 1 ? (size_t)Bf16Layout{d}.total_elems() * 2 : (size_t)F32Layout{d}.total_elems() * 4;
-  hipError_t e = set_max_lds_once<train_kernel<H, K, PREC, SEL>>(wmax + stage);
+  hipError_t e = set_max_lds_once<train_kernel<H, K, PREC, SEL, NW>>(wmax + stage);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(n_wg), dim3(64 * C::NW), shmem, st, a);
   return hipGetLastError();
 }
 
-template <int H, int K, int PREC>
+template <int H, int K, int PREC, int NW>
 static hipError_t launch_train_t(const TrainArgs& a, int n_wg, hipStream_t st) {
-  return a.sel ? launch_train_s<H, K, PREC, 1>(a, n_wg, st) : launch_train_s<H, K, PREC, 0>(a, n_wg, st);
+  return a.sel ? launch_train_s<H, K, PREC, 1, NW>(a, n_wg, st) : launch_train_s<H, K, PREC, 0, NW>(a, n_wg, st);
+}
+
+template <int H, int K, int PREC>
+static hipError_t launch_train_w(const TrainArgs& a, int n_wg, hipStream_t st) {
+  if constexpr (PREC == 1 || K < 16) {
+    if (train_is_wide(a.B, a.num_cus, K, PREC)) return launch_train_t<H, K, PREC, 8>(a, n_wg, st);
+  }
+  return launch_train_t<H, K, PREC, 4>(a, n_wg, st);
 }
 
 hipError_t launch_train(const TrainArgs& a, int H, int K, int prec, int n_wg, hipStream_t st) {
 #define NASG_CASE(h, k, p) \
-  if (H == h && K == k && prec == p) return launch_train_t<h, k, p>(a, n_wg, st);
+  if (H == h && K == k && prec == p) return launch_train_w<h, k, p>(a, n_wg, st);
   NASG_FOR_EACH_NET(NASG_CASE)
 #undef NASG_CASE
   return hipErrorInvalidValue;
