@@ -270,11 +270,16 @@ int train_workgroups(int64_t B, int num_cus) {
 // Eight waves over 128-vertex tiles (two waves per SIMD, so that one's LDS
 // round trips, barriers and NASG epilogue overlap the other's MFMAs) once
 // 64-vertex tiles would fill every CU, four over 64 below (twice the CUs, one
-// wave per SIMD). FP32 with K = 16: always four (its weights and the staging
-// of 128 vertices exceed the LDS). Measured (us per step, four / eight waves):
-// see train_kernel's figures beside launch_train.
+// wave per SIMD); the smaller BF16 networks, whose tiles are short beside the
+// sum over the workgroups' gradients, from half the CUs on. FP32 with K = 16:
+// always four (its weights and the staging of 128 vertices exceed the LDS).
+// Measured (us per step, four / eight waves): FP32 K = 8 4096 samples 32.2 /
+// 41.7, 16384 36.9 / 45.5, 20000 53.2 / 46.5, 2^18 288 / 246; BF16 K = 16 4096
+// 24.1 / 24.5, 16384 28.1 / 29.5, 20000 35.6 / 30.7, 2^18 148 / 105; K = 4
+// 4096 17.8 / 17.9, 16384 23.0 / 20.2.
 static bool train_is_wide(int64_t B, int num_cus, int K, int prec) {
-  return (prec == 1 || K < 16) && (B + kWGV - 1) / kWGV > num_cus;
+  const int64_t tiles = (B + kWGV - 1) / kWGV;
+  return prec == 1 ? (K == 16 ? tiles : 2 * tiles) > num_cus : K < 16 && tiles > num_cus;
 }
 
 int small_train_workgroups(int64_t B, int num_cus, int K, int prec) {
@@ -325,15 +330,48 @@ hipError_t launch_train(const TrainArgs& a, int H, int K, int prec, int n_wg, hi
 // as a binary tree too. Eight levels for 256 partials: the rounding error is
 // at most 8 u times the sum of the partials' magnitudes, and the result is
 // bitwise reproducible. Each block also writes its FP64 sum of grad^2 (the
-// gradient norm of the non-finite check); block 0 totals the FP64 loss
-// partials (strided per thread, then a fixed tree). n_weights is a multiple
+// gradient norm of the non-finite check). One more block beside them totals the
+// FP64 loss partials (strided per thread, then a fixed tree) and takes the
+// step snapshot and Adam's bias corrections, which therefore wait for nothing.
+// n_weights is a multiple
 // of 4 for every compiled network (checked on the host); at most 256
 // workgroup partials, 512 loss partials.
 constexpr int kRedW = 64;   // weights per block
 constexpr int kRedQ = 16;   // workgroup groups per block
 constexpr int kRedT = kMaxTrainWG / kRedQ;   // partial rows per group
 
+// The sum of a value over the block's 256 threads, on thread 0: by lane
+// exchange within each wave, then the four waves in order.
+__device__ __forceinline__ double block_sum(double x, double (&red)[4]) {
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) x += __shfl_xor(x, s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
 __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ double red_l[4], red_w[4];
+    // bias corrections of step t0 + 1 (used only if the step is taken)
+    const int64_t t0 = *a.step;
+    if (threadIdx.x == 64) a.corr[0] = a.lr / (float)(1.0 - pow((double)a.beta1, (double)(t0 + 1)));   // lr / (1 - beta1^t)
+    if (threadIdx.x == 128) a.corr[1] = (float)sqrt(1.0 - pow((double)a.beta2, (double)(t0 + 1)));     // sqrt(1 - beta2^t)
+    double ls = 0.0, ws = 0.0;
+    for (int wg = (int)threadIdx.x; wg < a.n_loss; wg += 256) {
+      ls += a.loss_partial[2 * wg];
+      ws += a.loss_partial[2 * wg + 1];
+    }
+    ls = block_sum(ls, red_l);
+    ws = block_sum(ws, red_w);
+    if (threadIdx.x == 0) {
+      a.stats[0] = ls / (double)a.B;
+      a.stats[1] = ws;
+      a.stats[3] = ls;
+      *a.step_snapshot = t0;
+    }
+    return;
+  }
   const int j = threadIdx.x & 15, q = threadIdx.x >> 4;
   const int64_t i0 = (int64_t)blockIdx.x * kRedW + 4 * j;
   float4 x[kRedT];
@@ -357,14 +395,12 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
       x[t].w += x[t + h].w;
     }
   __shared__ float part[kRedQ][kRedW];
-  __shared__ double red[256];
-  __shared__ double red_w[256];
   part[q][4 * j + 0] = x[0].x;
   part[q][4 * j + 1] = x[0].y;
   part[q][4 * j + 2] = x[0].z;
   part[q][4 * j + 3] = x[0].w;
   __syncthreads();
-  if (threadIdx.x < kRedW) {
+  if (threadIdx.x < kRedW) {   // one wave
     const int64_t i = (int64_t)blockIdx.x * kRedW + threadIdx.x;
     float g[kRedQ];
 #pragma unroll
@@ -375,55 +411,38 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
       for (int k = 0; k < h; ++k) g[k] += g[k + h];
     const float gf = g[0];
     if (i < a.n_weights) a.grad[i] = gf;
-    red[threadIdx.x] = i < a.n_weights ? (double)gf * (double)gf : 0.0;
-  }
-  __syncthreads();
-  for (int k = kRedW / 2; k >= 1; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.norm_partial[blockIdx.x] = red[0];
-  if (blockIdx.x == 0) {
-    __syncthreads();
-    double ls = 0.0, ws = 0.0;
-    for (int wg = (int)threadIdx.x; wg < a.n_loss; wg += 256) {
-      ls += a.loss_partial[2 * wg];
-      ws += a.loss_partial[2 * wg + 1];
-    }
-    red[threadIdx.x] = ls;
-    red_w[threadIdx.x] = ws;
-    __syncthreads();
-    for (int k = 128; k >= 1; k >>= 1) {
-      if ((int)threadIdx.x < k) {
-        red[threadIdx.x] += red[threadIdx.x + k];
-        red_w[threadIdx.x] += red_w[threadIdx.x + k];
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      a.stats[0] = red[0] / (double)a.B;
-      a.stats[1] = red_w[0];
-      a.stats[3] = red[0];
-      *a.step_snapshot = *a.step;
-    }
+    double nsq = i < a.n_weights ? (double)gf * (double)gf : 0.0;
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) nsq += __shfl_xor(nsq, s);
+    if (threadIdx.x == 0) a.norm_partial[blockIdx.x] = nsq;
   }
 }
 
 int reduce_blocks(int64_t n_weights) { return (int)((n_weights + kRedW - 1) / kRedW); }
 
 hipError_t launch_reduce(const ReduceArgs& a, int n_blocks, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(n_blocks), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(reduce_kernel, dim3(n_blocks + 1), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ adam ----
+// layer, row and column of canonical weight i (fewer than 2^31 of them; the
+// hidden layers' widths, 64 or 128, are powers of two)
 __device__ __forceinline__ void locate(const NetDims& d, int64_t i, int& l, int& n, int& k) {
-  l = 0;
-  for (int t = 1; t <= d.NH; ++t)
-    if (i >= d.canon_off(t)) l = t;
-  const int64_t r = i - d.canon_off(l);
-  n = (int)(r / d.cols(l));
-  k = (int)(r % d.cols(l));
+  const unsigned first = (unsigned)d.canon_off(1), hh = (unsigned)(d.H * d.H);
+  unsigned r = (unsigned)i;
+  if (r < first) {
+    l = 0;
+    n = d.E ? (int)(r / (unsigned)kInEncoded) : (int)(r / (unsigned)(kInFeatures + 1));
+    k = (int)r - n * d.in_cols();
+    return;
+  }
+  r -= first;
+  l = 1;
+  for (int t = 2; t <= d.NH; ++t)
+    if (r >= hh) { r -= hh; ++l; }
+  n = (int)(r / (unsigned)d.H);
+  k = (int)(r & (unsigned)(d.H - 1));
 }
 
 __device__ __forceinline__ void write_packed(const AdamArgs& a, const NetDims& d, int64_t i, float w) {
@@ -443,12 +462,16 @@ __device__ __forceinline__ void write_packed(const AdamArgs& a, const NetDims& d
 
 // Kingma and Ba's Adam, bias-corrected, no weight decay; skipped (weights,
 // moments and step unchanged, flag bit 0 set) if the loss or the gradient norm
-// is not finite. A thread's first element is loaded before the gradient norm
-// is summed, so the two memory latencies overlap; the bias corrections are
-// computed once per block, by two threads, during the norm sum.
+// is not finite. Bound by latency (21120 weights are 350 KB): a thread's first
+// element, the loss, the step, the bias corrections (reduce_kernel's) and its
+// share of the norm partials are requested together, and the norm is summed by
+// lane exchange. With double-precision powers and 64-bit divisions out of this
+// kernel and the loss totals in a block of their own, reduce and Adam went
+// from 4.2 + 4.9 us to 4.1 + 3.5 (K = 4, 64 partials), from 6.0 + 5.2 to 5.2 +
+// 4.8 (K = 16, 256) and from 4.8 + 6.4 to 4.8 + 4.8 (the hidden-128 K = 8
+// network, 32).
 __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
-  __shared__ double red[256];
-  __shared__ float corr[2];
+  __shared__ double red[4];
   const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * 256;
   float g0 = 0.0f, m0 = 0.0f, v0 = 0.0f, w0 = 0.0f;
@@ -459,20 +482,11 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
     w0 = a.w[i0];
   }
   const int64_t t0 = *a.step_snapshot;
-  // bias corrections of step t0 + 1 (used only if the step is taken),
-  // computed while the other threads sum the norm partials
-  if (threadIdx.x == 0) corr[0] = a.lr / (float)(1.0 - pow((double)a.beta1, (double)(t0 + 1)));   // lr / (1 - beta1^t)
-  if (threadIdx.x == 64) corr[1] = (float)sqrt(1.0 - pow((double)a.beta2, (double)(t0 + 1)));     // sqrt(1 - beta2^t)
+  const float step_size = a.corr[0], bc2_sqrt = a.corr[1];
+  const double loss = a.stats[0];
   double s = 0.0;
   for (int j = threadIdx.x; j < a.n_norm; j += 256) s += a.norm_partial[j];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k >= 1; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  const double nsq = red[0];
-  const double loss = a.stats[0];
+  const double nsq = block_sum(s, red);
   const bool skip = !isfinite(loss) || !isfinite(nsq);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.stats[2] = sqrt(nsq);
@@ -480,7 +494,6 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
     *a.step = skip ? t0 : t0 + 1;
   }
   if (skip) return;
-  const float step_size = corr[0], bc2_sqrt = corr[1];
   const NetDims d{a.H, a.NH, a.K, a.S, a.E};
   for (int64_t i = i0; i < a.n_weights; i += stride) {
     if (i != i0) {
