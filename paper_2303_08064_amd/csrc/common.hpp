@@ -152,6 +152,11 @@ __device__ __forceinline__ void lds_dma(void* lds, const void* src, int bytes) {
   }
 }
 
+// The LDS address of a pointer into LDS.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
+}
+
 // s_waitcnt vmcnt(0): every vector-memory load of this wave, including the
 // direct-to-LDS copies, has completed (expcnt and lgkmcnt left unconstrained).
 __device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }

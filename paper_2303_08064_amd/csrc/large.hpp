@@ -78,14 +78,27 @@ struct Pk {
         p[mt][k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v) * ind);
       }
   }
-  // write row tiles [MT0, MT0 + NMT) of the block into a [row][vertex]
-  // staging buffer (as its rows 0 ..) at vertex column wave*16
-  template <int SP, int MT0 = 0, int NMT = RT>
-  __device__ __forceinline__ void stage(__bf16* buf, int wave, int lane) const {
-    const int g = lane >> 4, c = lane & 15;
+  // write row tiles [MT0, MT0 + NMT) of the block into a staging buffer by
+  // vertex, of R rows (as its rows 0 ..)
+  template <int R, int MT0 = 0, int NMT = RT>
+  __device__ __forceinline__ void stage(void* buf, int wave, int lane) const {
+    // the addresses are formed here: hoisted out of the tile loop they do not
+    // fit beside the gradient tiles and come back from scratch memory (8 x 128
+    // K = 8 network, 2^18 samples: 341 -> 260 us; K = 32, 2^21: 2749 -> 2692)
+    asm volatile("" : "+v"(lane));
+    uint32_t w[NMT][2];
 #pragma unroll
-    for (int mt = 0; mt < NMT; ++mt)
-      stage_tile_bf16<SP>(buf + mt * 16 * SP + wave * 16, p[MT0 + mt][0], p[MT0 + mt][1], g, c);
+    for (int mt = 0; mt < NMT; ++mt) {
+      w[mt][0] = p[MT0 + mt][0];
+      w[mt][1] = p[MT0 + mt][1];
+    }
+    stage_words<R>(buf, w, wave, lane);
+  }
+  // the block into a staging buffer by row
+  template <int SP>
+  __device__ __forceinline__ void stage_rows(__bf16* buf, int wave, int lane) const {
+    asm volatile("" : "+v"(lane));
+    stage_words_rows<SP>(buf, p, wave, lane);
   }
 };
 
@@ -432,14 +445,14 @@ __device__ __forceinline__ void mask_relu(float (&d)[MTH][4], const Act<PREC, MT
     for (int i = 0; i < 4; ++i) d[mt][i] = h.get(mt, i) > 0.0f ? d[mt][i] : 0.0f;
 }
 
-template <typename S, int PREC, int MTH, int SP>
-__device__ __forceinline__ void stage_act(S* st, const Act<PREC, MTH>& h, int wave, int lane) {
+template <int PREC, int MTH, int SP>
+__device__ __forceinline__ void stage_act(float* st, const Act<PREC, MTH>& h, int wave, int lane) {
   float x[MTH][4];
 #pragma unroll
   for (int mt = 0; mt < MTH; ++mt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[mt][i] = h.get(mt, i);
-  stage_rows<S, MTH, SP>(st, x, wave, lane);
+  stage_rows_f32<MTH, SP>(st, x, wave, lane);
 }
 
 // dL/d(raw outputs) of 16 vertices: BF16 as the output layer's dgrad B
@@ -493,7 +506,7 @@ __global__ __launch_bounds__(256) void large_query_kernel(QueryArgs a) {
   typedef typename N::M M;
   typedef typename N::W W;
   constexpr int KQ = N::KQ;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   W* b0 = reinterpret_cast<W*>(smem);
   W* b1 = b0 + N::BUF;
   const W* wg = reinterpret_cast<const W*>(a.wpack);
@@ -541,7 +554,7 @@ __global__ __launch_bounds__(256) void gradout_kernel(LargeTrainArgs a) {
   typedef typename N::M M;
   typedef typename N::W W;
   constexpr int KQ = N::KQ, MTO = N::MTO;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   W* b0 = reinterpret_cast<W*>(smem);
   W* b1 = b0 + N::BUF;
   const W* wg = reinterpret_cast<const W*>(a.wpack);
@@ -604,9 +617,10 @@ __global__ __launch_bounds__(256) void gradout_kernel(LargeTrainArgs a) {
 // next tile's layer 0 resident.
 constexpr int kBwdWaves = 8;
 constexpr int kBwdV = 16 * kBwdWaves;   // vertices per backward tile
-// staging pitch (bf16): 144 values are 18 16-byte units, which makes the
-// weight-gradient operand reads free of LDS bank conflicts (units per row
-// 2 mod 4; 136 costs ~3 conflict cycles per 16-byte read on gfx950)
+// pitch of the inputs staged by row (bf16): 144 values are 18 16-byte units,
+// which makes the weight-gradient operand reads free of LDS bank conflicts
+// (units per row 2 mod 4; 136 costs ~3 conflict cycles per 16-byte read on
+// gfx950)
 constexpr int kBwdSP = kBwdV + 16;
 
 // LDS of the weight buffers, and of the backward kernels (weights + staging)
@@ -642,17 +656,22 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
   typedef __bf16 W;
   typedef __bf16 St;   // staging element
   typedef DOut<K, 1, SEL> DO;
-  constexpr int NH = N::NH, MTH = N::MTH, MTO = N::MTO, KBO = N::KBO, SP = kBwdSP;
+  constexpr int NH = N::NH, MTH = N::MTH, MTO = N::MTO, KBO = N::KBO;
+  // every wave reads all column tiles of a layer's input and one row tile of
+  // its deltas
+  typedef Staged<H> LD;
+  typedef Rows<kBwdSP> LI;
   constexpr int CTH = H / 16, HALF_H = MTH / 2, KBH = MTH / 2;
   constexpr int CT0 = M::IN / 16;                   // column tiles of layer 0
   static_assert(MTH == kBwdWaves, "one hidden row tile per wave");
   static_assert(N::NOUT == 2 ? MTO == 2 * kBwdWaves : MTO <= kBwdWaves, "output row tiles per wave");
   static_assert(MTO / N::NOUT * 16 <= H && M::IN <= H, "staging holds H rows");
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   W* bufA = reinterpret_cast<W*>(smem);
   W* bufB = bufA + N::BUF;
-  St* dst = reinterpret_cast<St*>(smem + 2 * N::BUF * sizeof(W));   // [H rows][SP]
-  St* hst = dst + H * SP;                                            // [H rows][SP]
+  St* dst = reinterpret_cast<St*>(smem + 2 * N::BUF * sizeof(W));   // deltas, H rows (Staged)
+  St* hst = dst + H * kBwdV;                                         // inputs, H rows (Rows)
+  static_assert(2 * N::BUF * sizeof(W) % 256 == 0, "aligned staging buffers");
   const W* wg = reinterpret_cast<const W*>(a.wpack);
   const Bf16Layout Lt = N::layout();
   const NetDims dims = Lt.d;
@@ -746,35 +765,35 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
       Pk<MTO> dlw;
       dlw.from_ops(bo);
       if constexpr (SEL == 1) dlw.set_last(bs);
-      hp[NH - 1].template stage<SP>(hst, wave, lane);
+      hp[NH - 1].template stage_rows<kBwdSP>(hst, wave, lane);
       if constexpr (N::NOUT == 2) {
-        dlw.template stage<SP, 0, MTH>(dst, wave, lane);           // output rows [0, 8K/2)
+        dlw.template stage<H, 0, MTH>(dst, wave, lane);           // output rows [0, 8K/2)
         N::dma(b1, out_bwd + N::OB_STAGE, N::OB_STAGE);
         dgrad_rows<KBO, HALF_H, 0, N::BM>(b0, bo, dh, lane);
         N::sync_stage();                                            // also publishes the staging
-        wgrad_tiles<1, St, SP, 1, CTH, kBwdV>(dst, hst, rt, 1, accO[0], lane);
+        wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accO[0][0], lane);
         N::dma(b0, wg + Lt.fwd_off(0), N::L0);                      // the next tile's layer 0
         dgrad_rows<KBO, HALF_H, HALF_H, N::BM>(b1, bo, dh, lane);
         dhw.masked(dh, hp[NH - 1]);
         N::sync_stage();                                            // the first half has been read
-        dlw.template stage<SP, MTH, MTH>(dst, wave, lane);          // output rows [8K/2, 8K)
+        dlw.template stage<H, MTH, MTH>(dst, wave, lane);          // output rows [8K/2, 8K)
         __syncthreads();
-        wgrad_tiles<1, St, SP, 1, CTH, kBwdV>(dst, hst, rt, 1, accO[N::NOUT - 1], lane);
+        wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accO[N::NOUT - 1][0], lane);
       } else {
-        dlw.template stage<SP, 0, MTO>(dst, wave, lane);            // every output row
+        dlw.template stage<16 * MTO, 0, MTO>(dst, wave, lane);            // every output row
         if constexpr (!RES) N::dma(b1, wg + Lt.fwd_off(0), N::L0);  // the next tile's layer 0
         dgrad_rows<KBO, MTH, 0, N::BM>(b0, bo, dh, lane);
         if constexpr (SEL == 1) dgrad_sel(b0 + 8 * K * H, bs, dh, lane);
         N::sync_stage();                                            // also publishes the staging
         N::swap(b0, b1);
-        wgrad_tiles<1, St, SP, 1, CTH, kBwdV>(dst, hst, rt, n_out_rt, accO[0], lane);
+        if (n_out_rt) wgrad_row<Staged<16 * MTO>, LI, CTH, kBwdV>(dst, hst, wave, accO[0][0], lane);
         dhw.masked(dh, hp[NH - 1]);
       }
       __syncthreads();
-      dhw.template stage<SP>(dst, wave, lane);
-      hp[NH - 2].template stage<SP>(hst, wave, lane);
+      dhw.template stage<H>(dst, wave, lane);
+      hp[NH - 2].template stage_rows<kBwdSP>(hst, wave, lane);
       __syncthreads();
-      wgrad_tiles<1, St, SP, 1, CTH, kBwdV>(dst, hst, rt, 1, accT, lane);
+      wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accT[0], lane);
       // the next writes to the staging area follow the next tile's forward,
       // whose barriers order them after these reads
     } else {
@@ -794,8 +813,8 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
       W* oth = b0;
 #pragma unroll
       for (int l = NH - 2; l >= 1; --l) {
-        d2w.template stage<SP>(dst, wave, lane);
-        hp[l - 1].template stage<SP>(hst, wave, lane);
+        d2w.template stage<H>(dst, wave, lane);
+        hp[l - 1].template stage_rows<kBwdSP>(hst, wave, lane);
         if (l > 1) N::dma(oth, wg + Lt.bwd_off(l - 1), H * H);
         else if (!RES) N::dma(oth, wg + Lt.fwd_off(0), N::L0);    // the next tile's layer 0
         bf16x8 op[KBH];
@@ -805,15 +824,15 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         Pk<MTH> dnw;
         dnw.masked(dn, hp[l - 1]);
         N::sync_stage();                                          // also publishes the staging
-        wgrad_tiles<1, St, SP, 1, CTH, kBwdV>(dst, hst, rt, 1, accM[l - 1], lane);
+        wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accM[l - 1][0], lane);
         __syncthreads();
         d2w = dnw;
         W* t = cur; cur = oth; oth = t;
       }
-      d2w.template stage<SP>(dst, wave, lane);
-      M::template stage_input<St, SP>(hst, x, wave, lane);
+      d2w.template stage<H>(dst, wave, lane);
+      stage_input_bf16(hst, x, wave, lane);
       __syncthreads();
-      wgrad_tiles<1, St, SP, 1, CT0, kBwdV>(dst, hst, rt, 1, acc0, lane);
+      wgrad_row<LD, Staged<M::IN>, CT0, kBwdV>(dst, hst, wave, acc0[0], lane);
       b0 = cur;   // the next tile's layer 0
       b1 = oth;
     }
@@ -877,7 +896,7 @@ void bwd_f32_kernel(LargeTrainArgs a) {
   constexpr int NH = N::NH, MTH = N::MTH, MTO = N::MTO, SP = N::SP;
   constexpr int RTW_H = (MTH + 3) / 4, RTW_O = (MTO + 3) / 4, CTH = H / 16;
   constexpr int CT0 = M::IN / 16;   // column tiles of layer 0
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   W* buf = reinterpret_cast<W*>(smem);
   S* dst = reinterpret_cast<S*>(smem + N::BUF * sizeof(W));
   S* hst = dst + N::RMAX * SP;
@@ -933,16 +952,16 @@ void bwd_f32_kernel(LargeTrainArgs a) {
     DOut<K, 0, SEL>::load(a.dout, tile * 4 + wave, dl, lane);
     float dh[MTH][4];
     if constexpr (GROUP == 0) {
-      stage_rows<S, MTO, SP>(dst, dl, wave, lane);
-      stage_act<S, 0, MTH, SP>(hst, hp[NH - 1], wave, lane);
+      stage_rows_f32<MTO, SP>(dst, dl, wave, lane);
+      stage_act<0, MTH, SP>(hst, hp[NH - 1], wave, lane);
       N::template dgrad_layer<MTO>(wg, buf, NH, dl, dh, lane);   // its weight staging publishes the above
       mask_relu<0, MTH>(dh, hp[NH - 1]);
-      wgrad_tiles<0, S, SP, RTW_O, CTH>(dst, hst, rt_o, nrt_o, accO, lane);
+      wgrad_tiles_f32<SP, RTW_O, CTH>(dst, hst, rt_o, nrt_o, accO, lane);
       __syncthreads();
-      stage_rows<S, MTH, SP>(dst, dh, wave, lane);
-      stage_act<S, 0, MTH, SP>(hst, hp[NH - 2], wave, lane);
+      stage_rows_f32<MTH, SP>(dst, dh, wave, lane);
+      stage_act<0, MTH, SP>(hst, hp[NH - 2], wave, lane);
       __syncthreads();
-      wgrad_tiles<0, S, SP, RTW_H, CTH>(dst, hst, rt_h, nrt_h, accT, lane);
+      wgrad_tiles_f32<SP, RTW_H, CTH>(dst, hst, rt_h, nrt_h, accT, lane);
       __syncthreads();
     } else {
       N::template dgrad_layer<MTO>(wg, buf, NH, dl, dh, lane);
@@ -952,22 +971,22 @@ void bwd_f32_kernel(LargeTrainArgs a) {
       mask_relu<0, MTH>(d2, hp[NH - 2]);
 #pragma unroll
       for (int l = NH - 2; l >= 1; --l) {
-        stage_rows<S, MTH, SP>(dst, d2, wave, lane);
-        stage_act<S, 0, MTH, SP>(hst, hp[l - 1], wave, lane);
+        stage_rows_f32<MTH, SP>(dst, d2, wave, lane);
+        stage_act<0, MTH, SP>(hst, hp[l - 1], wave, lane);
         float dn[MTH][4];
         N::template dgrad_layer<MTH>(wg, buf, l, d2, dn, lane);   // publishes the staging
         mask_relu<0, MTH>(dn, hp[l - 1]);
-        wgrad_tiles<0, S, SP, RTW_H, CTH>(dst, hst, rt_h, nrt_h, accM[l - 1], lane);
+        wgrad_tiles_f32<SP, RTW_H, CTH>(dst, hst, rt_h, nrt_h, accM[l - 1], lane);
         __syncthreads();
 #pragma unroll
         for (int mt = 0; mt < MTH; ++mt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) d2[mt][i] = dn[mt][i];
       }
-      stage_rows<S, MTH, SP>(dst, d2, wave, lane);
-      M::template stage_input<S, SP>(hst, x, wave, lane);
+      stage_rows_f32<MTH, SP>(dst, d2, wave, lane);
+      M::template stage_input<SP>(hst, x, wave, lane);
       __syncthreads();
-      wgrad_tiles<0, S, SP, RTW_H, CT0>(dst, hst, rt_h, nrt_h, acc0, lane);
+      wgrad_tiles_f32<SP, RTW_H, CT0>(dst, hst, rt_h, nrt_h, acc0, lane);
       __syncthreads();
     }
   }

@@ -89,23 +89,6 @@ struct Mlp<H, K, 1, E> {
     return bf16x4{(__bf16)f[0], (__bf16)f[1], (__bf16)f[2], (__bf16)f[3]};
   }
 
-  // layer 0's input (the values the forward used) into rows 0..IN-1 of a
-  // [row][vertex] staging buffer at vertex column wave*16: rows 4g..4g+3, or
-  // for the encoded input rows kb*32 + 8g .. + 7
-  template <typename S, int SP>
-  __device__ __forceinline__ static void stage_input(S* st, const Input& x, int wave, int lane) {
-    const int g = lane >> 4, c = lane & 15;
-    if constexpr (E == 1) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) st[(kb * 32 + 8 * g + j) * SP + wave * 16 + c] = (S)x.b[kb][j];
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) st[(4 * g + j) * SP + wave * 16 + c] = (S)x[j];
-    }
-  }
-
   __device__ __forceinline__ static bf16x8 operand(const float (&in)[2][4]) {
     bf16x8 b;
 #pragma unroll
@@ -328,14 +311,15 @@ struct Mlp<H, K, 0, E> {
     return in;
   }
 
-  // layer 0's input into rows 0..IN-1 of a staging buffer: rows kb*4 + g
-  // hold this lane's x.x[kb]; for the raw input rows 12..15 are zero padding
-  template <typename S, int SP>
-  __device__ __forceinline__ static void stage_input(S* st, const Input& x, int wave, int lane) {
+  // layer 0's input into rows 0..IN-1 of a staging buffer [row][vertex]: rows
+  // kb*4 + g hold this lane's x.x[kb]; for the raw input rows 12..15 are zero
+  // padding
+  template <int SP>
+  __device__ __forceinline__ static void stage_input(float* st, const Input& x, int wave, int lane) {
     const int g = lane >> 4, c = lane & 15;
 #pragma unroll
-    for (int kb = 0; kb < KB0; ++kb) st[(kb * 4 + g) * SP + wave * 16 + c] = (S)x.x[kb];
-    if constexpr (E == 0) st[(12 + g) * SP + wave * 16 + c] = (S)0.0f;
+    for (int kb = 0; kb < KB0; ++kb) st[(kb * 4 + g) * SP + wave * 16 + c] = x.x[kb];
+    if constexpr (E == 0) st[(12 + g) * SP + wave * 16 + c] = 0.0f;
   }
 
   __device__ __forceinline__ static void layer0(const float* lds, const Input& x, float (&h)[MTH][4], int lane) {

@@ -32,28 +32,36 @@ struct TrainCfg {
   static constexpr int CTH = H / 16;            // column tiles of dW (hidden input)
   static constexpr int NW = NW_;
   static constexpr int NV = 16 * NW;            // vertices per tile
-  static constexpr int RMAX = (16 * MTO > H) ? 16 * MTO : H;   // rows of the largest delta
-  // staging pitch (elements). BF16: a row of NV + 16 = 144 values is 18
-  // 16-byte units; the weight-gradient operand reads (lane (g, c): 16 B of
-  // row c at unit g) are free of LDS bank conflicts when the row's units are
-  // 2 mod 4 (measured on gfx950: 136, 152, 160, 168 and 184 values per row
-  // each cost ~3 conflict cycles per read, 144 and 176 none). The selection
-  // networks' staging at 144 would exceed the LDS beside their weights, so
-  // they keep 136 (80 with four waves is free too). FP32: conflict-free at NV
-  // + 4 (a row's 16-byte units 1 mod 16, so 16 rows cover the banks).
-  static constexpr int SP = PREC == 1 ? (SEL == 1 && NW == 8 ? NV + 8 : NV + 16) : NV + 4;
+  static constexpr int RO = 16 * MTO;           // rows of the output layer's delta
+  static constexpr int RMAX = RO > H ? RO : H;  // rows of the largest delta
+  // staging layouts: of the output layer's deltas and of its input (staged by
+  // row in BF16: every wave reads all of its column tiles), of the hidden
+  // layers' deltas and inputs, of layer 0's input. BF16 by row: a row of NV +
+  // 16 values is 18 (four waves: 10) 16-byte units; the reads of lane (g, c), 16
+  // B of row c at unit g, are free of LDS bank conflicts when a row's units
+  // are 2 mod 4 (measured on gfx950: 136, 152, 160, 168 and 184 values per row
+  // each cost ~3 conflict cycles per read, 144 and 176 none). FP32, one 16-byte
+  // read of four vertices: free at NV + 4 (units 1 mod 16, so 16 rows cover the
+  // banks).
+  static constexpr int SP = PREC == 1 ? NV + 16 : NV + 4;
+  typedef typename std::conditional<PREC == 1, Staged<RO>, RowsF32<SP>>::type DO;
+  typedef typename std::conditional<PREC == 1, Rows<SP>, RowsF32<SP>>::type HO;
+  typedef typename std::conditional<PREC == 1, Staged<H>, RowsF32<SP>>::type LH;
+  typedef typename std::conditional<PREC == 1, Staged<16>, RowsF32<SP>>::type L0;
   typedef Own<MTH, 1, NW> O0;                   // layer 0
   typedef Own<MTH, CTH, NW> OH;                 // hidden layers
   typedef Own<MTO, CTH, NW> OO;                 // output layer
   // BF16: the hidden layers and layer 0 alternate between two staging
   // buffers, so a layer's writes never meet the previous layer's weight-
   // gradient reads and one barrier per layer suffices. The second delta
-  // buffer is rows H..2H-1 of the first where the output layer's delta
-  // (RMAX rows) leaves room, else rows of its own, like the second input
+  // buffer is the second half of the first where the output layer's delta
+  // (RMAX rows) leaves room, else one of its own, like the second input
   // buffer (all BF16 networks fit the 160 KiB of LDS with it).
   static constexpr bool DB = PREC == 1;
-  static constexpr int EXTRA = DB ? (RMAX >= 2 * H ? H : 2 * H) : 0;   // staging rows of the second buffer
-  static constexpr int stage_elems() { return (RMAX + H + EXTRA) * SP; }
+  static constexpr bool SHARED = RMAX >= 2 * H;   // the second delta buffer within the first
+  static constexpr int PV = PREC == 1 ? NV : SP;  // elements per delta row
+  static constexpr int delta_elems() { return RMAX * PV; }
+  static constexpr int stage_elems() { return delta_elems() + H * SP + (DB ? (SHARED ? H : 2 * H) * PV : 0); }
 };
 
 // weights of layer l in LDS (forward and, for l >= 1, backward)
@@ -70,6 +78,9 @@ struct TrainLds {
   }
 };
 
+// the packed weights' place in LDS: the staging after them is 256-byte aligned
+__host__ __device__ constexpr int train_weight_bytes(int bytes) { return (bytes + 255) / 256 * 256; }
+
 // SEL = 1: the network has the selection output and the loss is the blend
 // of Sec. 4.2 (the BSDF pdf at each training direction is an input)
 template <int H, int K, int PREC, int SEL, int NW_>
@@ -82,13 +93,13 @@ void train_kernel(TrainArgs a) {
   typedef typename TL::W W;
   constexpr int NHMAX = C::NHMAX, KQ = C::KQ, MTH = C::MTH, MTO = C::MTO, SP = C::SP, NW = C::NW, NV = C::NV;
   constexpr int CTH = C::CTH;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(256) unsigned char smem[];
   W* lds = reinterpret_cast<W*>(smem);
-  S* dst = reinterpret_cast<S*>(smem + a.lds_bytes);     // delta staging [RMAX][SP]
-  S* hst = dst + C::RMAX * SP;                            // input staging [H][SP]
-  // the second staging buffer (C::DB): delta [H][SP], input [H][SP]
-  S* dstB = C::RMAX >= 2 * H ? dst + H * SP : hst + H * SP;
-  S* hstB = C::RMAX >= 2 * H ? hst + H * SP : dstB + H * SP;
+  S* dst = reinterpret_cast<S*>(smem + train_weight_bytes(a.lds_bytes));   // delta staging, RMAX rows
+  S* hst = dst + C::delta_elems();                                         // input staging, H rows
+  // the second staging buffer (C::DB): delta and input, H rows each
+  S* dstB = C::SHARED ? dst + H * C::PV : hst + H * SP;
+  S* hstB = C::SHARED ? hst + H * SP : dstB + H * C::PV;
   lds_dma(lds, a.wpack, a.lds_bytes);
 
   const int lane = lane_id();
@@ -173,21 +184,27 @@ void train_kernel(TrainArgs a) {
     float dh[MTH][4];
     uint32_t dw[MTH][2];
     {
-      stage_rows<S, MTO, SP>(dst, dl, wave, lane);
+      if constexpr (PREC == 1) {
+        uint32_t dlw[MTO][2];
+        pack_rows(dl, dlw);
+        stage_words<C::RO>(dst, dlw, wave, lane);
+      } else {
+        stage_rows_f32<MTO, SP>(dst, dl, wave, lane);
+      }
       dgrad<H, K, PREC, MTO>(TL::bwd(lds, nh, nh), dl, dh, lane);
       if constexpr (PREC == 1) {
-        stage_words<MTH, SP>(hst, lastw, wave, lane);
+        stage_words_rows<SP>(hst, lastw, wave, lane);
         pack_rows(dh, dw);
         mask_rows(dw, lastw);
       } else {
-        stage_rows<S, MTH, SP>(hst, last, wave, lane);
+        stage_rows_f32<MTH, SP>(hst, last, wave, lane);
 #pragma unroll
         for (int mt = 0; mt < MTH; ++mt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) dh[mt][i] = last[mt][i] > 0.0f ? dh[mt][i] : 0.0f;
       }
       __syncthreads();
-      wgrad_own<PREC, S, SP, MTO, CTH, NW, NV>(dst, hst, acco, wave, lane);
+      wgrad_own<PREC, typename C::DO, typename C::HO, MTO, CTH, NW, NV>(dst, hst, acco, wave, lane);
       __syncthreads();
     }
     // ---- hidden layers l = nh-1 .. 1 ----
@@ -202,15 +219,15 @@ void train_kernel(TrainArgs a) {
       S* const hs = alt ? hstB : hst;
       float dn[MTH][4];
       if constexpr (PREC == 1) {
-        stage_words<MTH, SP>(ds, dw, wave, lane);
-        stage_words<MTH, SP>(hs, hw[l - 1], wave, lane);
+        stage_words<H>(ds, dw, wave, lane);
+        stage_words<H>(hs, hw[l - 1], wave, lane);
         dgrad_words<H, MTH>(TL::bwd(lds, l, nh), dw, dn, lane);
         pack_rows(dn, dw);
         mask_rows(dw, hw[l - 1]);
       } else {
         const float (&prev)[MTH][4] = h[l - 1];
-        stage_rows<S, MTH, SP>(ds, dh, wave, lane);
-        stage_rows<S, MTH, SP>(hs, prev, wave, lane);
+        stage_rows_f32<MTH, SP>(ds, dh, wave, lane);
+        stage_rows_f32<MTH, SP>(hs, prev, wave, lane);
         dgrad<H, K, PREC, MTH>(TL::bwd(lds, l, nh), dh, dn, lane);
 #pragma unroll
         for (int mt = 0; mt < MTH; ++mt)
@@ -218,7 +235,7 @@ void train_kernel(TrainArgs a) {
           for (int i = 0; i < 4; ++i) dh[mt][i] = prev[mt][i] > 0.0f ? dn[mt][i] : 0.0f;
       }
       __syncthreads();
-      wgrad_own<PREC, S, SP, MTH, CTH, NW, NV>(ds, hs, acch[l - 1], wave, lane);
+      wgrad_own<PREC, typename C::LH, typename C::LH, MTH, CTH, NW, NV>(ds, hs, acch[l - 1], wave, lane);
       if constexpr (!C::DB) __syncthreads();
     }
     // ---- layer 0: input = features, constant one, zero padding ----
@@ -226,11 +243,15 @@ void train_kernel(TrainArgs a) {
       constexpr bool alt = C::DB && ((NHMAX - 1) & 1);
       S* const ds = alt ? dstB : dst;
       S* const hs = alt ? hstB : hst;
-      if constexpr (PREC == 1) stage_words<MTH, SP>(ds, dw, wave, lane);
-      else stage_rows<S, MTH, SP>(ds, dh, wave, lane);
-      M::template stage_input<S, SP>(hs, x, wave, lane);
+      if constexpr (PREC == 1) {
+        stage_words<H>(ds, dw, wave, lane);
+        stage_input_bf16(hs, x, wave, lane);
+      } else {
+        stage_rows_f32<MTH, SP>(ds, dh, wave, lane);
+        M::template stage_input<SP>(hs, x, wave, lane);
+      }
       __syncthreads();
-      wgrad_own<PREC, S, SP, MTH, 1, NW, NV>(ds, hs, acc0, wave, lane);
+      wgrad_own<PREC, typename C::LH, typename C::L0, MTH, 1, NW, NV>(ds, hs, acc0, wave, lane);
       __syncthreads();   // the next tile's output layer writes both buffers' rows
     }
   }
@@ -290,12 +311,12 @@ template <int H, int K, int PREC, int SEL, int NW>
 static hipError_t launch_train_s(const TrainArgs& a, int n_wg, hipStream_t st) {
   typedef TrainCfg<H, K, PREC, SEL, NW> C;
   const size_t stage = sizeof(typename C::S) * C::stage_elems();
-  const size_t shmem = (size_t)a.lds_bytes + stage;
+  const size_t shmem = (size_t)train_weight_bytes(a.lds_bytes) + stage;
   auto kern = train_kernel<H, K, PREC, SEL, NW>;
   // the largest footprint of this network shape (4 hidden layers)
   const NetDims d{H, C::NHMAX, K, SEL};
   const size_t wmax = PREC == 1 ? (size_t)Bf16Layout{d}.total_elems() * 2 : (size_t)F32Layout{d}.total_elems() * 4;
-  hipError_t e = set_max_lds_once<train_kernel<H, K, PREC, SEL, NW>>(wmax + stage);
+  hipError_t e = set_max_lds_once<train_kernel<H, K, PREC, SEL, NW>>(train_weight_bytes((int)wmax) + stage);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(n_wg), dim3(64 * C::NW), shmem, st, a);
   return hipGetLastError();
