@@ -40,6 +40,8 @@ namespace nasg {
 // move between layers, masks and LDS staging without conversions.
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+
 template <int RT>
 struct Pk {
   uint32_t p[RT][2];
@@ -62,20 +64,27 @@ struct Pk {
     for (int kb = 0; kb < RT / 2; ++kb)
       b[kb] = __builtin_bit_cast(bf16x8, u32x4{p[2 * kb][0], p[2 * kb][1], p[2 * kb + 1][0], p[2 * kb + 1][1]});
   }
-  // bf16(d) where the activation h of the same row is > 0, else 0 (the ReLU
-  // derivative). h holds ReLU outputs, so its halves are non-negative
-  // integers: min(h, 1) is the 0/1 indicator and a 16-bit multiply applies it.
-  __device__ __forceinline__ void masked(const float (&d)[RT][4], const Pk& h) {
+  // 0/1 indicators (16 bits each) of word (mt, k)'s halves being > 0, of ReLU
+  // outputs: their halves are non-negative integers, so min(h, 1) is it
+  __device__ __forceinline__ u16x2 positive(int mt, int k) const {
+    // written out: the compiler makes this minimum a compare and a select for
+    // each half
+    uint32_t ind;
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(ind) : "v"(p[mt][k]), "s"(0x00010001u));
+    return __builtin_bit_cast(u16x2, ind);
+  }
+  // bf16(d) where the activation h (a Pk or a Signs) of the same row is > 0,
+  // else 0 (the ReLU derivative): a 16-bit multiply applies the indicator.
+  template <typename Hidden>
+  __device__ __forceinline__ void masked(const float (&d)[RT][4], const Hidden& h) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     typedef __attribute__((ext_vector_type(2))) float f32x2;
-    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
 #pragma unroll
     for (int mt = 0; mt < RT; ++mt)
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const bf16x2 v = __builtin_convertvector((f32x2){d[mt][2 * k], d[mt][2 * k + 1]}, bf16x2);
-        const u16x2 ind = __builtin_elementwise_min(__builtin_bit_cast(u16x2, h.p[mt][k]), (u16x2)1);
-        p[mt][k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v) * ind);
+        p[mt][k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v) * h.positive(mt, k));
       }
   }
   // write row tiles [MT0, MT0 + NMT) of the block into a staging buffer by
@@ -99,6 +108,25 @@ struct Pk {
   __device__ __forceinline__ void stage_rows(__bf16* buf, int wave, int lane) const {
     asm volatile("" : "+v"(lane));
     stage_words_rows<SP>(buf, p, wave, lane);
+  }
+};
+
+// The signs alone of a layer's activations, for layers that a kernel needs
+// only as ReLU derivatives: bit j (j + 16) of m is the indicator of the low
+// (high) half of word j, one register in place of 2 RT.
+template <int RT>
+struct Signs {
+  static_assert(RT <= 8, "16 words");
+  uint32_t m;
+  __device__ __forceinline__ void from_ops(const bf16x8 (&b)[RT / 2]) {
+    Pk<RT> h;
+    h.from_ops(b);
+    m = 0;
+#pragma unroll
+    for (int j = 0; j < 2 * RT; ++j) m |= __builtin_bit_cast(uint32_t, h.positive(j / 2, j % 2)) << j;
+  }
+  __device__ __forceinline__ u16x2 positive(int mt, int k) const {
+    return __builtin_bit_cast(u16x2, (m >> (2 * mt + k)) & 0x00010001u);
   }
 };
 
@@ -192,10 +220,11 @@ struct NetBf16 {
     sync_stage();
   }
 
-  // Hidden layers of one tile with layer 0 resident in b0: hp[l] receives
+  // Hidden layers of one tile with layer 0 resident in b0: keep(l, b) receives
   // hidden layer l's activations as B operands; `next` (elems) is resident
   // in b0 on return (a full forward puts the output layer's first stage there).
-  __device__ __forceinline__ static void hidden(const W* wg, W*& b0, W*& b1, const typename M::Input& x, Pk<MTH> (&hp)[NH],
+  template <typename Keep>
+  __device__ __forceinline__ static void hidden(const W* wg, W*& b0, W*& b1, const typename M::Input& x, Keep keep,
                                 const W* next, int next_elems, int lane) {
     const Bf16Layout Lt = layout();
     float y[MTH][4];
@@ -203,7 +232,7 @@ struct NetBf16 {
     dma(b1, wg + Lt.fwd_off(1), H * H);
     M::layer0_linear(b0, x, y, lane);
     M::relu_operands(y, b);
-    hp[0].from_ops(b);
+    keep(0, b);
     sync_stage();
 #pragma unroll
     for (int l = 1; l < NH; ++l) {
@@ -213,18 +242,16 @@ struct NetBf16 {
       else dma(oth, next, next_elems);
       M::template gemm_op<MTH, BM>(cur, b, y, lane);
       M::relu_operands(y, b);
-      hp[l].from_ops(b);
+      keep(l, b);
       sync_stage();
     }
   }
 
   // Output layer from the last hidden layer's activations, with its first
   // stage resident in b0; leaves `next` (elems) resident in b0 on return.
-  __device__ __forceinline__ static void output(const W* wg, W*& b0, W*& b1, const Pk<MTH>& hl, float (&out)[MTO][4],
-                                const W* next, int next_elems, int lane) {
+  __device__ __forceinline__ static void output(const W* wg, W*& b0, W*& b1, const bf16x8 (&b)[M::KBH],
+                                float (&out)[MTO][4], const W* next, int next_elems, int lane) {
     const Bf16Layout Lt = layout();
-    bf16x8 b[M::KBH];
-    hl.ops(b);
     if constexpr (NOUT == 2) {
       dma(b1, wg + Lt.fwd_off(NH) + OUT_STAGE, OUT_STAGE);
       {
@@ -259,27 +286,34 @@ struct NetBf16 {
   __device__ __forceinline__ static void forward(const W* wg, W*& b0, W*& b1, const typename M::Input& x, float (&out)[MTO][4],
                                  int lane) {
     const Bf16Layout Lt = layout();
-    Pk<MTH> hp[NH];
-    hidden(wg, b0, b1, x, hp, wg + Lt.fwd_off(NH), OUT_STAGE, lane);   // output stage 0 -> b0
-    output(wg, b0, b1, hp[NH - 1], out, wg + Lt.fwd_off(0), L0, lane);
+    bf16x8 h[M::KBH];
+    auto keep = [&](int l, const bf16x8 (&b)[M::KBH]) {
+      if (l == NH - 1) {
+#pragma unroll
+        for (int kb = 0; kb < M::KBH; ++kb) h[kb] = b[kb];
+      }
+    };
+    hidden(wg, b0, b1, x, keep, wg + Lt.fwd_off(NH), OUT_STAGE, lane);   // output stage 0 -> b0
+    output(wg, b0, b1, h, out, wg + Lt.fwd_off(0), L0, lane);
   }
 
   // Forward of one tile with every forward weight resident at `base` in the
   // packed forward order (FWD elements): no stage waits.
   static constexpr int FWD = L0 + (NH - 1) * H * H + OUT;
-  __device__ __forceinline__ static void forward_resident(const W* base, const typename M::Input& x, Pk<MTH> (&hp)[NH],
+  template <typename Keep>
+  __device__ __forceinline__ static void forward_resident(const W* base, const typename M::Input& x, Keep keep,
                                           float (&out)[MTO][4], int lane) {
     const Bf16Layout Lt = layout();
     float y[MTH][4];
     bf16x8 b[M::KBH];
     M::layer0_linear(base, x, y, lane);
     M::relu_operands(y, b);
-    hp[0].from_ops(b);
+    keep(0, b);
 #pragma unroll
     for (int l = 1; l < NH; ++l) {
       M::template gemm_op<MTH, BM>(base + Lt.fwd_off(l), b, y, lane);
       M::relu_operands(y, b);
-      hp[l].from_ops(b);
+      keep(l, b);
     }
     M::template gemm_op<MTO, BM>(base + Lt.fwd_off(NH), b, out, lane);
   }
@@ -481,6 +515,16 @@ struct DOut {
     }
   }
   // BF16: the stored slots are exactly the output layer's dgrad B operands
+  __device__ __forceinline__ static void operands(const float (&dl)[MTO][4], bf16x8 (&b)[KBO], bf16x4& bs) {
+#pragma unroll
+    for (int kb = 0; kb < KBO; ++kb)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) b[kb][j] = (__bf16)dl[2 * kb + (j >> 2)][j & 3];
+    if constexpr (SEL == 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bs[j] = (__bf16)dl[MTO - 1][j];
+    }
+  }
   __device__ __forceinline__ static void store_operands(void* base, int64_t tile16, const bf16x8 (&b)[KBO], const bf16x4& bs,
                                         int lane) {
     __bf16* blk = reinterpret_cast<__bf16*>(base) + tile16 * BLOCK;
@@ -635,10 +679,10 @@ struct LargeLds {
 };
 
 
-// One workgroup's share of a backward group: tiles wg, wg + n_wg, ... OWN
-// (group 0 only): evaluate the loss gradient itself (the forward's output
-// layer and the epilogue) instead of reading group 1's stored one, so that
-// the two groups can run at the same time.
+// One workgroup's share of a backward group: tiles wg, wg + n_wg, ... OWN:
+// evaluate the loss gradient here (the forward's output layer and the
+// epilogue): group 1, whose copy is stored for group 0, and group 0 where the
+// two run at the same time; else read the stored one.
 // SINGLE: the workgroup has one tile at most, so the tile loop has no back
 // edge and the gradient accumulators are live from their first MFMA only
 // (not across the forward and the epilogue). RES (SINGLE, loss gradient
@@ -648,10 +692,11 @@ struct LargeLds {
 template <int H, int K, int SEL, int ENC, int GROUP, bool OWN, bool SINGLE = false, bool RES = false>
 __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, int n_wg) {
   // block-major MFMA order where the registers allow it: everywhere but the
-  // multi-tile group-1 kernel, whose gradient accumulators stay live across
-  // the forward and the epilogue
-  typedef NetBf16<H, K, SEL, ENC, GROUP == 0 || SINGLE> N;
-  static_assert(!RES || (SINGLE && (GROUP == 1 || OWN)), "the resident forward: one tile, loss gradient here");
+  // multi-tile group-1 kernel of K = 32, whose gradient accumulators stay
+  // live across the forward and a four times larger epilogue (2^21 samples:
+  // K = 32 2387 us block-major, 2325 row by row; K = 8 1614 and 1690)
+  typedef NetBf16<H, K, SEL, ENC, GROUP == 0 || SINGLE || K <= 8> N;
+  static_assert(!RES || (SINGLE && OWN), "the resident forward: one tile, loss gradient here");
   typedef typename N::M M;
   typedef __bf16 W;
   typedef __bf16 St;   // staging element
@@ -711,10 +756,25 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
     const int64_t blk = tile * kBwdWaves + wave;   // this wave's 16-vertex block
     const bool valid = v < a.B;
     typename M::Input x = M::load_input(a.feat, a.ld, v, valid, g);
+    // group 1 stages the inputs of layers NH-2 .. 0 and needs only the signs
+    // of the last two hidden layers' activations: 28 registers fewer across
+    // the epilogue, beside the gradient tiles (K = 32: its kernel 4.0 -> 3.26
+    // ms at 2^22 samples, of it 0.1 from the masks' form in Pk::positive).
+    // Group 0 stages both.
     Pk<MTH> hp[NH];
+    Signs<MTH> sg[NH];
+    bf16x8 hl[KBH];
+    auto keep = [&](int l, const bf16x8 (&b)[KBH]) {
+      if (GROUP == 0 || l < NH - 2) hp[l].from_ops(b);
+      else sg[l].from_ops(b);
+      if (OWN && l == NH - 1) {
+#pragma unroll
+        for (int kb = 0; kb < KBH; ++kb) hl[kb] = b[kb];
+      }
+    };
     bf16x8 bo[KBO];
     bf16x4 bs = {};
-    if constexpr (GROUP == 1 || OWN) {
+    if constexpr (OWN) {
       float vx = 0.0f, vy = 0.0f, vz = 1.0f, wj = 0.0f, pfs = 0.0f;
       if (valid) {
         vx = a.dir[v]; vy = a.dir[a.ld + v]; vz = a.dir[2 * a.ld + v];
@@ -726,12 +786,12 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         __syncthreads();                                                        // a previous tile's staging is read
         N::dma(bufA, wg, N::FWD);
         N::sync_stage();
-        N::forward_resident(bufA, x, hp, out, lane);
+        N::forward_resident(bufA, x, keep, out, lane);
         __syncthreads();                                                        // the forward image is consumed
         N::dma(b0, out_bwd, N::OB_STAGE);                                       // awaited after the epilogue
       } else {
-        N::hidden(wg, b0, b1, x, hp, wg + Lt.fwd_off(NH), N::OUT_STAGE, lane);  // output stage 0 -> b0
-        N::output(wg, b0, b1, hp[NH - 1], out, out_bwd, N::OB_STAGE, lane);    // output-dgrad stage 0 -> b0
+        N::hidden(wg, b0, b1, x, keep, wg + Lt.fwd_off(NH), N::OUT_STAGE, lane);  // output stage 0 -> b0
+        N::output(wg, b0, b1, hl, out, out_bwd, N::OB_STAGE, lane);    // output-dgrad stage 0 -> b0
       }
       const float inv = frsq(fmaf(vx, vx, fmaf(vy, vy, vz * vz)));
       vx *= inv; vy *= inv; vz *= inv;
@@ -743,20 +803,11 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         loss_sum += (double)wj * (double)(-lterm);
         w_sum += (double)wj;
       }
-#pragma unroll
-      for (int kb = 0; kb < KBO; ++kb)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) bo[kb][j] = (__bf16)dl[2 * kb + (j >> 2)][j & 3];
-      if constexpr (SEL == 1) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bs[j] = (__bf16)dl[MTO - 1][j];
-      }
-      // stored for the separate group-0 kernel only (in the one-launch
-      // schedule group 0 evaluates its own)
-      if constexpr (GROUP == 1 && !SINGLE) DO::store_operands(a.dout, blk, bo, bs, lane);
+      DO::operands(dl, bo, bs);
+      if constexpr (!SINGLE) DO::store_operands(a.dout, blk, bo, bs, lane);
       if constexpr (RES) N::sync_stage();                                       // output-dgrad stage 0 in b0
     } else {
-      N::hidden(wg, b0, b1, x, hp, out_bwd, N::OB_STAGE, lane);   // leaves output-dgrad stage 0 in b0
+      N::hidden(wg, b0, b1, x, keep, out_bwd, N::OB_STAGE, lane);   // leaves output-dgrad stage 0 in b0
       DO::load_operands(a.dout, blk, bo, bs, lane);
     }
     float dh[MTH][4];
@@ -798,7 +849,7 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
       // whose barriers order them after these reads
     } else {
       N::out_dgrad(out_bwd, b0, b1, bo, bs, dh, wg + Lt.bwd_off(NH - 1), H * H, lane);   // layer NH-1 -> b0
-      dhw.masked(dh, hp[NH - 1]);
+      dhw.masked(dh, sg[NH - 1]);
       Pk<MTH> d2w;
       {
         bf16x8 op[KBH];
@@ -806,7 +857,7 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         float d2[MTH][4];
         N::dma(b1, wg + Lt.bwd_off(NH - 2), H * H);
         dgrad_rows<KBH, MTH, 0, N::BM>(b0, op, d2, lane);                // through hidden layer NH-1
-        d2w.masked(d2, hp[NH - 2]);
+        d2w.masked(d2, sg[NH - 2]);
         N::sync_stage();
       }
       W* cur = b1;   // holds hidden layer l's backward fragments
@@ -848,6 +899,8 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
 #pragma unroll
     for (int l = 1; l <= NH - 2; ++l) flush_tiles<1, CTH>(part, dims, l, rt, 1, accM[l - 1], lane);
     flush_tiles<1, CT0>(part, dims, 0, rt, 1, acc0, lane);
+  }
+  if constexpr (GROUP == 1 && OWN) {
     // loss partials: wave reduction, then the waves in order
     __shared__ double red[kBwdWaves][2];
 #pragma unroll
@@ -878,10 +931,10 @@ void bwd_bf16_kernel(LargeTrainArgs a) {
     // one tile per workgroup here; the forward image fits the LDS for K = 8
     constexpr bool RES = NetBf16<H, K, SEL, ENC>::FWD <= LargeLds<H, K, 1, SEL, ENC>::bwd / 2;
     const int half = (int)(gridDim.x >> 1);
-    if ((int)blockIdx.x < half) bwd_bf16_body<H, K, SEL, ENC, 1, false, true, RES>(a, (int)blockIdx.x, half);
+    if ((int)blockIdx.x < half) bwd_bf16_body<H, K, SEL, ENC, 1, true, true, RES>(a, (int)blockIdx.x, half);
     else bwd_bf16_body<H, K, SEL, ENC, 0, true, true, RES>(a, (int)blockIdx.x - half, half);
   } else {
-    bwd_bf16_body<H, K, SEL, ENC, GROUP, false>(a, (int)blockIdx.x, (int)gridDim.x);
+    bwd_bf16_body<H, K, SEL, ENC, GROUP, GROUP == 1>(a, (int)blockIdx.x, (int)gridDim.x);
   }
 }
 
