@@ -242,7 +242,7 @@ __device__ __forceinline__ void mask_rows(uint32_t (&d)[RT][2], const uint32_t (
   for (int mt = 0; mt < RT; ++mt)
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const u16x2 ind = __builtin_elementwise_min(__builtin_bit_cast(u16x2, h[mt][k]), (u16x2)1);
+      const u16x2 ind = __builtin_bit_cast(u16x2, relu_indicator(h[mt][k]));
       d[mt][k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, d[mt][k]) * ind);
     }
 }

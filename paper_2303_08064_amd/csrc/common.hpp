@@ -99,6 +99,15 @@ __device__ __forceinline__ void mfma_rows(const bf16x8* frag, BOp bop, f32x4 (&a
   }
 }
 
+// 0/1 indicators (16 bits each) of a pair of BF16 ReLU outputs being > 0:
+// their halves are non-negative integers, so min(h, 1) is it. Written out: the
+// compiler makes this minimum a compare and a select for each half.
+__device__ __forceinline__ uint32_t relu_indicator(uint32_t h) {
+  uint32_t ind;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(ind) : "v"(h), "s"(0x00010001u));
+  return ind;
+}
+
 // The FP32 counterpart for MT row tiles and KQ 16-wide contraction blocks:
 // acc[mt] = sum over kq, i of A(mt, kq)[i] b(kq, i), chained in that order,
 // A(mt, kq) being the lane's four operands of block kq (one 16-byte LDS read).

@@ -21,17 +21,24 @@ struct EncodedInput {
   bf16x8 b[2];
 };
 
-__device__ __forceinline__ EncodedInput load_encoded(const float* __restrict__ feat, int64_t ld, int64_t v,
-                                                     bool valid, int g) {
-  float p[3] = {0.0f, 0.0f, 0.0f}, dn[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  if (valid) {
+// The features a lane's part of the encoded input is made of: the position,
+// and omega_o and n for lane group 3.
+struct EncodedRaw {
+  float p[3], dn[6];
+};
+
+__device__ __forceinline__ EncodedRaw load_encoded(const float* __restrict__ feat, int64_t ld, int64_t v) {
+  EncodedRaw r;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) p[i] = feat[(int64_t)i * ld + v];
-    if (g == 3) {
+  for (int i = 0; i < 3; ++i) r.p[i] = feat[(int64_t)i * ld + v];
 #pragma unroll
-      for (int i = 0; i < 6; ++i) dn[i] = feat[(int64_t)(3 + i) * ld + v];
-    }
-  }
+  for (int i = 0; i < 6; ++i) r.dn[i] = feat[(int64_t)(3 + i) * ld + v];
+  return r;
+}
+
+__device__ __forceinline__ EncodedInput encode(const EncodedRaw& raw, bool valid, int g) {
+  const float (&p)[3] = raw.p;
+  const float (&dn)[6] = raw.dn;
   constexpr float kHalfLog2e = 0.72134752044448170368f;   // log2(e) / 2
   EncodedInput x;
 #pragma unroll
@@ -68,25 +75,42 @@ struct Mlp<H, K, 1, E> {
   static constexpr int IN = E ? kInEncoded : kInPadded;   // layer 0's packed input width
   typedef typename std::conditional<E == 1, EncodedInput, bf16x4>::type Input;
 
-  // features 4g..4g+3 of vertex v: p, omega_o, n, then the constant one, then
-  // zeros; or the encoded input
-  __device__ __forceinline__ static Input load_input(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
-    if constexpr (E == 1) return load_encoded(feat, ld, v, valid, g);
-    else return load_raw(feat, ld, v, valid, g);
-  }
-  __device__ __forceinline__ static bf16x4 load_raw(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
-    float f[4];
+  // A lane's part of vertex v's input in two steps, so that a caller can have
+  // the loads in flight beside other work: the features that it is made of,
+  // loaded without a branch (v must be a vertex of the batch; lanes without a
+  // feature read another one of it), and the operand once they are needed:
+  // features 4g..4g+3 (p, omega_o, n, then the constant one, then zeros), or
+  // the encoded input; zero where not valid.
+  struct FourRaw { float f[4]; };
+  typedef typename std::conditional<E == 1, EncodedRaw, FourRaw>::type Raw;
+  __device__ __forceinline__ static Raw load_raw(const float* __restrict__ feat, int64_t ld, int64_t v, int g) {
+    if constexpr (E == 1) {
+      return load_encoded(feat, ld, v);
+    } else {
+      Raw r;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int k = 4 * g + j;
-      float x = 0.0f;
-      if (valid) {
-        if (k < kInFeatures) x = feat[(int64_t)k * ld + v];
-        else if (k == kInFeatures) x = 1.0f;
-      }
-      f[j] = x;
+      for (int j = 0; j < 4; ++j) r.f[j] = feat[(int64_t)min(4 * g + j, kInFeatures - 1) * ld + v];
+      return r;
     }
-    return bf16x4{(__bf16)f[0], (__bf16)f[1], (__bf16)f[2], (__bf16)f[3]};
+  }
+  __device__ __forceinline__ static Input input(const Raw& r, bool valid, int g) {
+    if constexpr (E == 1) {
+      return encode(r, valid, g);
+    } else {
+      float f[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = 4 * g + j;
+        f[j] = valid && k <= kInFeatures ? (k < kInFeatures ? r.f[j] : 1.0f) : 0.0f;
+      }
+      return bf16x4{(__bf16)f[0], (__bf16)f[1], (__bf16)f[2], (__bf16)f[3]};
+    }
+  }
+  // both at once, from any v
+  __device__ __forceinline__ static Input load_input(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
+    Raw r = {};
+    if (valid) r = load_raw(feat, ld, v, g);
+    return input(r, valid, g);
   }
 
   __device__ __forceinline__ static bf16x8 operand(const float (&in)[2][4]) {
@@ -267,20 +291,27 @@ struct Mlp<H, K, 0, E> {
   // inputs kb*4 + g for kb < KB0
   struct Input { float x[KB0]; };
 
-  // raw: features, then the constant one, then zeros. Encoded (the same
-  // inputs as the BF16 network's): one-blob bin k % 19 of position
+  // In two steps as the BF16 network's. Raw input: features, then the
+  // constant one, then zeros. Encoded: one-blob bin k % 19 of position
   // coordinate k / 19 for k < 57, then omega_o, n and the constant one.
-  __device__ __forceinline__ static Input load_input(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
+  struct Raw { float f[E ? 5 : KB0]; };   // encoded: p, omega_o[g - 1], n[g]
+  __device__ __forceinline__ static Raw load_raw(const float* __restrict__ feat, int64_t ld, int64_t v, int g) {
+    Raw r;
+    if constexpr (E == 1) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) r.f[i] = feat[(int64_t)i * ld + v];
+      r.f[3] = feat[(int64_t)(3 + max(g - 1, 0)) * ld + v];
+      r.f[4] = feat[(int64_t)(6 + min(g, 2)) * ld + v];
+    } else {
+#pragma unroll
+      for (int kb = 0; kb < KB0; ++kb) r.f[kb] = feat[(int64_t)min(kb * 4 + g, kInFeatures - 1) * ld + v];
+    }
+    return r;
+  }
+  __device__ __forceinline__ static Input input(const Raw& r, bool valid, int g) {
     Input in;
     if constexpr (E == 1) {
-      float p[3] = {0.0f, 0.0f, 0.0f};
-      float wo = 0.0f, nn = 0.0f;
-      if (valid) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) p[i] = feat[(int64_t)i * ld + v];
-        if (g >= 1) wo = feat[(int64_t)(3 + g - 1) * ld + v];   // k = 56 + g: omega_o[g - 1]
-        if (g <= 2) nn = feat[(int64_t)(6 + g) * ld + v];       // k = 60 + g: n[g]
-      }
+      const float wo = r.f[3], nn = r.f[4];   // k = 56 + g: omega_o[g - 1]; k = 60 + g: n[g]
       constexpr float kHalfLog2e = 0.72134752044448170368f;   // log2(e) / 2
 #pragma unroll
       for (int kb = 0; kb < KB0; ++kb) {
@@ -290,7 +321,7 @@ struct Mlp<H, K, 0, E> {
         else if (kb == 15) val = g == 3 ? 1.0f : nn;
         else {
           const int d = (k >= 2 * kBlobBins) ? 2 : (k >= kBlobBins ? 1 : 0);
-          const float s = d == 0 ? p[0] : (d == 1 ? p[1] : p[2]);
+          const float s = d == 0 ? r.f[0] : (d == 1 ? r.f[1] : r.f[2]);
           const float t = fmaf(s, (float)kBlobBins, -((float)(k - kBlobBins * d) + 0.5f));
           val = __builtin_amdgcn_exp2f(-kHalfLog2e * t * t);
         }
@@ -299,16 +330,16 @@ struct Mlp<H, K, 0, E> {
     } else {
 #pragma unroll
       for (int kb = 0; kb < KB0; ++kb) {
-        int k = kb * 4 + g;
-        float x = 0.0f;
-        if (valid) {
-          if (k < kInFeatures) x = feat[(int64_t)k * ld + v];
-          else if (k == kInFeatures) x = 1.0f;
-        }
-        in.x[kb] = x;
+        const int k = kb * 4 + g;
+        in.x[kb] = valid && k <= kInFeatures ? (k < kInFeatures ? r.f[kb] : 1.0f) : 0.0f;
       }
     }
     return in;
+  }
+  __device__ __forceinline__ static Input load_input(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
+    Raw r = {};
+    if (valid) r = load_raw(feat, ld, v, g);
+    return input(r, valid, g);
   }
 
   // layer 0's input into rows 0..IN-1 of a staging buffer [row][vertex]: rows
