@@ -554,12 +554,20 @@ __global__ __launch_bounds__(256) void large_query_kernel(QueryArgs a) {
   const int wave = threadIdx.x >> 6;
   if constexpr (PREC == 1) N::begin(wg, b0);
   const int64_t n_tiles = (a.B + kWGV - 1) / kWGV;
+  // the next tile's inputs are requested before a tile's epilogue (lanes past
+  // the batch read its last vertex; their results are not stored)
+  auto load = [&](int64_t tile) {
+    const int64_t v = tile * kWGV + wave * 16 + c;
+    return M::load_raw(a.feat, a.ld, v < a.B ? v : a.B - 1, g);
+  };
+  typename M::Raw in = load(blockIdx.x);
   for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const int64_t v = tile * kWGV + wave * 16 + c;
     const bool valid = v < a.B;
-    typename M::Input x = M::load_input(a.feat, a.ld, v, valid, g);
+    const typename M::Input x = M::input(in, true, g);
     float out[N::MTO][4];
     N::forward(wg, b0, b1, x, out, lane);
+    in = load(tile + gridDim.x);
     if constexpr (MODE == 1) {
       if (valid) {
 #pragma unroll

@@ -88,26 +88,6 @@ __device__ __forceinline__ void stage_pass32(const QueryArgs& a, int64_t tile, f
   }
 }
 
-// Layer 0's input of vertex `col` of a staged pass, as the Mlp's load_input:
-// of the 9 features, the constant one, then zeros, lane group g holds 4g ..
-// 4g + 3 (BF16) or g, 4 + g, 8 + g (FP32)
-template <typename M, int PREC>
-__device__ __forceinline__ typename M::Input staged_input(const float* buf, int col, bool valid, int g) {
-  auto at = [&](int k) {
-    float x = 0.0f;
-    if (valid) {
-      if (k < kInFeatures) x = buf[k * 64 + col];
-      else if (k == kInFeatures) x = 1.0f;
-    }
-    return x;
-  };
-  if constexpr (PREC == 1) {
-    return bf16x4{(__bf16)at(4 * g), (__bf16)at(4 * g + 1), (__bf16)at(4 * g + 2), (__bf16)at(4 * g + 3)};
-  } else {
-    return {{at(g), at(4 + g), at(8 + g)}};
-  }
-}
-
 // MODE 0: query, 1: raw forward only, 2: query that also stores the decoded
 // records (a kernel of its own: the store's addresses and the raw outputs
 // that it needs raise the K = 16 kernel from 224 to 256 registers); S = 1:
@@ -142,21 +122,20 @@ void query_kernel(QueryArgs a) {
   const int lane = lane_id();
   const int g = lane >> 4, c = lane & 15;
   const int wave = threadIdx.x >> 6;
-  // inputs of one block of a one-block pass
+  // inputs of one block of a one-block pass, without branches (a branch waits
+  // for its loads); lanes past the batch read, as in the staged passes, its
+  // last vertex, and their results are not stored
   struct BlockIn {
-    typename M::Input x;
+    typename M::Raw x;
     float xi[4];
   };
   auto load_block = [&](int64_t block) {
     BlockIn in;
-    const int64_t v = block * kTileV + c;
-    in.x = M::load_input(a.feat, a.ld, v, v < a.B, g);
+    int64_t v = block * kTileV + c;
+    v = v < a.B ? v : a.B - 1;
+    in.x = M::load_raw(a.feat, a.ld, v, g);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) in.xi[r] = 0.0f;
-    if (MODE != 1 && v < a.B) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) in.xi[r] = a.xi[r * a.ld + v];
-    }
+    for (int r = 0; r < 4; ++r) in.xi[r] = MODE != 1 ? a.xi[r * a.ld + v] : 0.0f;
     return in;
   };
   // one-block passes: four waves of a workgroup (one per SIMD) take
@@ -196,8 +175,8 @@ void query_kernel(QueryArgs a) {
       query_epilogue<KQ, S, 4, REC, SPLIT, F::MTO>(
           a, tile * (4 * kTileV), lane,
           [&](int b, float (&out)[F::MTO][4]) {
-            const bool valid = tile * (4 * kTileV) + b * kTileV + c < a.B;
-            F::template run_query<BM>(wts, a.nh, staged_input<M, PREC>(cur, b * kTileV + c, valid, g), out, lane);
+            const typename M::Input x = M::input(M::load_raw(cur, 64, b * kTileV + c, g), true, g);
+            F::template run_query<BM>(wts, a.nh, x, out, lane);
           },
           [&](int r, int i) { return cur[(kInFeatures + r) * 64 + i]; });
     }
@@ -208,13 +187,14 @@ void query_kernel(QueryArgs a) {
   const int64_t stride = (int64_t)gridDim.x * NW;
   if constexpr (NB == 1) {
     for (BlockIn in = first; block < n_tiles; in = load_block(block)) {
+      const typename M::Input x = M::input(in.x, true, g);
       if constexpr (MODE == 1) {
         float out[F::MTO][4];
-        F::template run_query<BM>(wts, a.nh, in.x, out, lane);
+        F::template run_query<BM>(wts, a.nh, x, out, lane);
         store_raw<K, S>(a, out, block * kTileV + c, g);
       } else {
         query_epilogue<KQ, S, 1, REC, false, F::MTO>(
-            a, block * kTileV, lane, [&](int, float (&out)[F::MTO][4]) { F::template run_query<BM>(wts, a.nh, in.x, out, lane); },
+            a, block * kTileV, lane, [&](int, float (&out)[F::MTO][4]) { F::template run_query<BM>(wts, a.nh, x, out, lane); },
             [&](int r, int) { return in.xi[r]; });
       }
       block += stride;
@@ -237,10 +217,7 @@ void query_kernel(QueryArgs a) {
       }
       typename M::Input x[NB];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int64_t v = tile * TV + nb * kTileV + c;
-        x[nb] = M::load_input(cur, 32, nb * kTileV + c, v < a.B, g);
-      }
+      for (int nb = 0; nb < NB; ++nb) x[nb] = M::input(M::load_raw(cur, 32, nb * kTileV + c, g), true, g);
       float out[NB][F::MTO][4];
       F::template run_query_nb<NB, MODE != 1>(wts, a.nh, x, out, lane);
       if constexpr (MODE == 1) {
