@@ -267,25 +267,38 @@ __device__ __forceinline__ void dgrad_words(const void* wl, const uint32_t (&dw)
     for (int i = 0; i < 4; ++i) dp[mt][i] = acc[0][mt][i];
 }
 
-// acc[ct] += D[rows rt*16..][v] * Hs[cols ct*16..][v]^T over the NV vertices
-// staged in BF16 in the layouts DL and HL
-template <typename DL, typename HL, int NC, int NV>
-__device__ __forceinline__ void wgrad_row(const void* dst, const void* hst, int rt, f32x4 (&acc)[NC], int lane) {
+// acc[r][ct] += D[rows (r0+r)*16..][v] * Hs[cols (c0+ct)*16..][v]^T over the
+// NV vertices staged in BF16 in the layouts DL and HL
+template <typename DL, typename HL, int NV, int NR, int NC>
+__device__ __forceinline__ void wgrad_block(const void* dst, const void* hst, int r0, int c0, f32x4 (&acc)[NR][NC],
+                                            int lane) {
   asm volatile("" : "+v"(lane));   // addresses formed here, not kept across the kernel
   const int g = lane >> 4, c = lane & 15;
   const uint32_t db = DL::read_base(dst, g, c), hb = HL::read_base(hst, g, c);
 #pragma unroll
   for (int vb = 0; vb < NV / 32; ++vb) {
-    bf16x8 h[NC];
+    bf16x8 h[NC], d[NR];
 #pragma unroll
-    for (int ct = 0; ct < NC; ++ct) h[ct] = HL::operand(hb, ct, vb);
-    const bf16x8 da = DL::operand(db, rt, vb);
+    for (int ct = 0; ct < NC; ++ct) h[ct] = HL::operand(hb, c0 + ct, vb);
 #pragma unroll
-    for (int ct = 0; ct < NC; ++ct) acc[ct] = mfma_bf16_32(da, h[ct], acc[ct]);
+    for (int r = 0; r < NR; ++r) d[r] = DL::operand(db, r0 + r, vb);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int ct = 0; ct < NC; ++ct) acc[r][ct] = mfma_bf16_32(d[r], h[ct], acc[r][ct]);
   }
 }
 
-// The same for several row tiles in FP32 ([row][vertex], pitch SP).
+template <int NR, int NC>
+__device__ __forceinline__ void zero_tiles(f32x4 (&acc)[NR][NC]) {
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int ct = 0; ct < NC; ++ct) acc[r][ct] = zero4();
+}
+
+// The same for all column tiles and a wave's row tiles in FP32 ([row][vertex],
+// pitch SP).
 template <int SP, int NR, int NC, int NV = kWGV>
 __device__ __forceinline__ void wgrad_tiles_f32(const float* dst, const float* hst, const int (&rt)[NR], int nrt,
                                                 f32x4 (&acc)[NR][NC], int lane) {
@@ -406,7 +419,7 @@ __device__ __forceinline__ void flush_own(float* part, const NetDims& d, int l,
 // PAD: the tiles may hold the selection tile's padding rows (skipped).
 template <int NR, int NC, bool PAD = false>
 __device__ __forceinline__ void flush_tiles(float* part, const NetDims& d, int l, const int (&rt)[NR], int nrt,
-                                            const f32x4 (&acc)[NR][NC], int lane) {
+                                            const f32x4 (&acc)[NR][NC], int lane, int c0 = 0) {
   const int g = lane >> 4, c = lane & 15;
   const int cols = d.cols(l);
   const int64_t off = d.canon_off(l);
@@ -415,7 +428,7 @@ __device__ __forceinline__ void flush_tiles(float* part, const NetDims& d, int l
     if (r >= nrt) continue;
 #pragma unroll
     for (int ct = 0; ct < NC; ++ct) {
-      const int k = ct * 16 + c;
+      const int k = (c0 + ct) * 16 + c;
       if (k >= cols) continue;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -425,6 +438,16 @@ __device__ __forceinline__ void flush_tiles(float* part, const NetDims& d, int l
       }
     }
   }
+}
+
+// The same for a block of tiles (wgrad_block's).
+template <bool PAD, int NR, int NC>
+__device__ __forceinline__ void flush_block(float* part, const NetDims& d, int l, int r0, int c0,
+                                            const f32x4 (&acc)[NR][NC], int lane) {
+  int rt[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) rt[r] = r0 + r;
+  flush_tiles<NR, NC, PAD>(part, d, l, rt, NR, acc, lane, c0);
 }
 
 }  // namespace nasg

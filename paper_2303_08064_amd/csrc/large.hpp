@@ -727,26 +727,28 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
   const int lane = lane_id();
   const int g = lane >> 4, c = lane & 15;
   const int wave = threadIdx.x >> 6;
-  const int rt[1] = {wave};                 // this wave's row tile (+ MTH for a two-stage output layer)
-  const int rt_hi[1] = {wave + MTH};
-  const int n_out_rt = (N::NOUT == 2 || wave < MTO) ? 1 : 0;   // output row tiles this wave owns
+  // this wave's tiles of each weight gradient: two row by four column tiles of
+  // a hidden layer (and of each half of a two-stage output layer), one column
+  // tile of a one-stage output layer, two by CT0/2 of layer 0
+  const int r0 = wave & ~1, c0 = (wave & 1) * (CTH / 2);
+  constexpr int RO = N::NOUT == 2 ? 2 : MTO, CO = N::NOUT == 2 ? CTH / 2 : 1;
+  const int ro = N::NOUT == 2 ? r0 : 0, co = N::NOUT == 2 ? c0 : wave;
+  constexpr int R0 = CT0 > 1 ? 2 : 1, C0 = CT0 > 1 ? CT0 / 2 : 1;
+  const int ri = CT0 > 1 ? r0 : wave, ci = CT0 > 1 ? (wave & 1) * C0 : 0;
+  static_assert(CTH == kBwdWaves && CTH % 2 == 0 && (CT0 == 1 || CT0 % 2 == 0), "column tiles per wave");
 
   constexpr int NO = GROUP == 0 ? N::NOUT : 1;      // output layer stages (group 0)
   constexpr int NM = GROUP == 1 ? NH - 2 : 1;       // hidden layers NH-2..1 (group 1)
-  f32x4 accO[NO][1][CTH];
-  f32x4 accT[1][CTH];                               // layer NH-1 (group 0)
-  f32x4 accM[NM][1][CTH];
-  f32x4 acc0[1][CT0];                               // layer 0 (group 1)
+  f32x4 accO[NO][RO][CO];
+  f32x4 accT[2][CTH / 2];                           // layer NH-1 (group 0)
+  f32x4 accM[NM][2][CTH / 2];
+  f32x4 acc0[R0][C0];                               // layer 0 (group 1)
+  zero_tiles(acc0);
+  zero_tiles(accT);
 #pragma unroll
-  for (int ct = 0; ct < CT0; ++ct) acc0[0][ct] = zero4();
+  for (int l = 0; l < NM; ++l) zero_tiles(accM[l]);
 #pragma unroll
-  for (int ct = 0; ct < CTH; ++ct) {
-    accT[0][ct] = zero4();
-#pragma unroll
-    for (int l = 0; l < NM; ++l) accM[l][0][ct] = zero4();
-#pragma unroll
-    for (int h = 0; h < NO; ++h) accO[h][0][ct] = zero4();
-  }
+  for (int h = 0; h < NO; ++h) zero_tiles(accO[h]);
 
   const float inv_b = 1.0f / (float)a.B;
   double loss_sum = 0.0, w_sum = 0.0;
@@ -842,14 +844,14 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         N::dma(b1, out_bwd + N::OB_STAGE, N::OB_STAGE);
         dgrad_rows<KBO, HALF_H, 0, N::BM>(b0, bo, dh, lane);
         N::sync_stage();                                            // also publishes the staging
-        wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accO[0][0], lane);
+        wgrad_block<LD, LI, kBwdV>(dst, hst, ro, co, accO[0], lane);
         N::dma(b0, wg + Lt.fwd_off(0), N::L0);                      // the next tile's layer 0
         dgrad_rows<KBO, HALF_H, HALF_H, N::BM>(b1, bo, dh, lane);
         dhw.masked(dh, hp[NH - 1]);
         N::sync_stage();                                            // the first half has been read
         dlw.template stage<H, MTH, MTH>(dst, wave, lane);          // output rows [8K/2, 8K)
         __syncthreads();
-        wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accO[N::NOUT - 1][0], lane);
+        wgrad_block<LD, LI, kBwdV>(dst, hst, ro, co, accO[N::NOUT - 1], lane);
       } else {
         dlw.template stage<16 * MTO, 0, MTO>(dst, wave, lane);            // every output row
         if constexpr (!RES) N::dma(b1, wg + Lt.fwd_off(0), N::L0);  // the next tile's layer 0
@@ -857,7 +859,7 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         if constexpr (SEL == 1) dgrad_sel(b0 + 8 * K * H, bs, dh, lane);
         N::sync_stage();                                            // also publishes the staging
         N::swap(b0, b1);
-        if (n_out_rt) wgrad_row<Staged<16 * MTO>, LI, CTH, kBwdV>(dst, hst, wave, accO[0][0], lane);
+        wgrad_block<Staged<16 * MTO>, LI, kBwdV>(dst, hst, ro, co, accO[0], lane);
         dhw.masked(dh, hp[NH - 1]);
       }
       __syncthreads();
@@ -865,7 +867,7 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
       hp[NH - 2].template stage_rows<kBwdSP>(hst, wave, lane);
       if constexpr (!SINGLE) in = load_in(tile + n_wg);
       __syncthreads();
-      wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accT[0], lane);
+      wgrad_block<LD, LI, kBwdV>(dst, hst, r0, c0, accT, lane);
       // the next writes to the staging area follow the next tile's forward,
       // whose barriers order them after these reads
     } else {
@@ -896,7 +898,7 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
         Pk<MTH> dnw;
         dnw.masked(dn, hp[l - 1]);
         N::sync_stage();                                          // also publishes the staging
-        wgrad_row<LD, LI, CTH, kBwdV>(dst, hst, wave, accM[l - 1][0], lane);
+        wgrad_block<LD, LI, kBwdV>(dst, hst, r0, c0, accM[l - 1], lane);
         __syncthreads();
         d2w = dnw;
         W* t = cur; cur = oth; oth = t;
@@ -905,7 +907,7 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
       stage_input_bf16(hst, x, wave, lane);
       if constexpr (!SINGLE) in = load_in(tile + n_wg);
       __syncthreads();
-      wgrad_row<LD, Staged<M::IN>, CT0, kBwdV>(dst, hst, wave, acc0[0], lane);
+      wgrad_block<LD, Staged<M::IN>, kBwdV>(dst, hst, ri, ci, acc0, lane);
       b0 = cur;   // the next tile's layer 0
       b1 = oth;
     }
@@ -914,13 +916,13 @@ __device__ __forceinline__ void bwd_bf16_body(const LargeTrainArgs& a, int wgi, 
 
   float* part = a.partial + (int64_t)wgi * a.n_weights;
   if constexpr (GROUP == 0) {
-    flush_tiles<1, CTH, SEL == 1>(part, dims, NH, rt, n_out_rt, accO[0], lane);
-    if constexpr (N::NOUT == 2) flush_tiles<1, CTH>(part, dims, NH, rt_hi, 1, accO[N::NOUT - 1], lane);
-    flush_tiles<1, CTH>(part, dims, NH - 1, rt, 1, accT, lane);
+    flush_block<SEL == 1>(part, dims, NH, ro, co, accO[0], lane);
+    if constexpr (N::NOUT == 2) flush_block<false>(part, dims, NH, MTH + ro, co, accO[N::NOUT - 1], lane);
+    flush_block<false>(part, dims, NH - 1, r0, c0, accT, lane);
   } else {
 #pragma unroll
-    for (int l = 1; l <= NH - 2; ++l) flush_tiles<1, CTH>(part, dims, l, rt, 1, accM[l - 1], lane);
-    flush_tiles<1, CT0>(part, dims, 0, rt, 1, acc0, lane);
+    for (int l = 1; l <= NH - 2; ++l) flush_block<false>(part, dims, l, r0, c0, accM[l - 1], lane);
+    flush_block<false>(part, dims, 0, ri, ci, acc0, lane);
   }
   if constexpr (GROUP == 1 && OWN) {
     // loss partials: wave reduction, then the waves in order
