@@ -79,19 +79,18 @@ __device__ __forceinline__ float exp2m1_neg(float z, Const) {
 struct ConstOne { static constexpr float k = 1.0f; };
 struct Const2Log2e { static constexpr float k = 2.0f * kLog2e; };
 
-// log(1 - w) for 0 <= w < 1/16: y (1 + y (d0 + d1 y + d2 y^2 + d3 y^3)) with
-// y = -w, the minimax fit of relative error on [-1/16, 0] with the linear
-// term held at y (Remez exchange; fit error 4e-10 relative).
-__device__ __forceinline__ float log1m_poly(float w) {
-  const float y = -w;
-  float r = fmaf(y, 0.227763459f, -0.248499244f);
-  r = fmaf(y, r, 0.333364844f);
-  r = fmaf(y, r, -0.499999791f);
-  return y * fmaf(y, r, 1.0f);
+// log(1 - w) from w4 = 4 w, for 0 <= w < 1/16: y (1 + y (d0 + d1 y + d2 y^2 +
+// d3 y^3)) with y = -w, the minimax fit of relative error on [-1/16, 0] with
+// the linear term held at y (Remez exchange; fit error 4e-10 relative), its
+// coefficients scaled by powers of 4, which is exact.
+__device__ __forceinline__ float log1m_poly4(float w4) {
+  float r = fmaf(w4, 0.227763459f * (-1.0f / 1024.0f), -0.248499244f * (1.0f / 256.0f));
+  r = fmaf(w4, r, 0.333364844f * (-1.0f / 64.0f));
+  r = fmaf(w4, r, -0.499999791f * (1.0f / 16.0f));
+  return w4 * fmaf(w4, r, -0.25f);
 }
 
-// log2(1 - w) from w4 = 4 w: log1m_poly with its coefficients and variable
-// scaled by powers of 4 (exact) and the coefficients by log2 e.
+// log2(1 - w) from w4: log1m_poly4 with its coefficients times log2 e.
 __device__ __forceinline__ float log2_1m_poly4(float w4) {
   constexpr float e = kLog2e;
   float r = fmaf(w4, 0.227763459f * (-1.0f / 1024.0f) * e, -0.248499244f * (1.0f / 256.0f) * e);
@@ -126,6 +125,7 @@ struct Lobe {
 // Euler-angle intermediates kept for the backward pass.
 struct LobeAux {
   float ct, st, cp, sp, ctau, stau;
+  float hst;                // st / 2
   float h1, h2, h3, h4;     // (1 - d_i^2)/2 = 2 e_i / (1 + e_i)^2 for the sin/cos pairs
   float inv_np, inv_nt;     // 1/|(d2,d1)|, 1/|(d4,d3)|
   float loglam, loga;       // clamped raw values
@@ -139,9 +139,9 @@ __device__ __forceinline__ void unit_pair(float c, float s, float& cu, float& su
   float n2 = fmaf(c, c, s * s);
   inv = frsq(n2);
   bool ok = n2 > 0.0f;
-  cu = fsel(ok, c * inv, 1.0f);
-  su = fsel(ok, s * inv, 0.0f);
   inv = fsel(ok, inv, 0.0f);
+  cu = fsel(ok, c * inv, 1.0f);
+  su = s * inv;
 }
 
 // log(2 pi) + log(one_m) - loglam - (1/2) log((1+eps)(1+eps+a)), the two
@@ -195,8 +195,8 @@ __device__ __forceinline__ void decode_pair(float oc, float os, float& cu, float
   unit_pair(copysignf(mc * ts, oc), copysignf(ms * tc, os), cu, su, inv);
   inv_n = tc * ts * inv;                             // 1/|(tanh(oc/2), tanh(os/2))|
   const float rc = ts * R, rs = tc * R;              // 1/(2 - mc), 1/(2 - ms)
-  hc = 2.0f * (1.0f - mc) * rc * rc;
-  hs = 2.0f * (1.0f - ms) * rs * rs;
+  hc = fmaf(-2.0f, mc, 2.0f) * rc * rc;
+  hs = fmaf(-2.0f, ms, 2.0f) * rs * rs;
 }
 
 // amul = 0 decodes isotropic lobes (a = 0: the normalised spherical
@@ -207,7 +207,8 @@ __device__ __forceinline__ void decode_lobe(const float o[8], float eps, Lobe& L
   const float e0 = h0 * h0;
   const float r0 = frcp(1.0f + e0);
   X.ct = copysignf((1.0f - e0) * r0, o[0]);
-  X.st = 2.0f * h0 * r0;                             // sech(o/2) = sqrt(1 - tanh^2)
+  X.hst = h0 * r0;
+  X.st = 2.0f * X.hst;                               // sech(o/2) = sqrt(1 - tanh^2)
   decode_pair(o[2], o[1], X.cp, X.sp, X.inv_np, X.h2, X.h1);
   decode_pair(o[4], o[3], X.ctau, X.stau, X.inv_nt, X.h4, X.h3);
   L.zx = X.cp * X.st;
@@ -312,15 +313,15 @@ __device__ __forceinline__ Eval eval_lobe(const Lobe& L, float vx, float vy, flo
   cross(L.zx, L.zy, L.zz, L.xx, L.xy, L.xz, yx, yy, yz);
   float dx = vx - L.zx, dy = vy - L.zy, dz = vz - L.zz;
   float sx = vx + L.zx, sy = vy + L.zy, sz = vz + L.zz;
-  float w = 0.25f * fmaf(dx, dx, fmaf(dy, dy, dz * dz));   // 1 - u
+  float w4 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));          // 4 (1 - u)
   float u = 0.25f * fmaf(sx, sx, fmaf(sy, sy, sz * sz));   // u
-  // log u: a polynomial in w for log(1 - w) near the axis, else the log of the
-  // better-conditioned of 1 - w and u (one log either way)
-  float lw = log1m_poly(w);
-  float lu = flog(fsel(w <= 0.5f, 1.0f - w, u));
-  r.L = fsel(w < 0.0625f, lw, lu);
+  // log u, w = 1 - u = w4 / 4: a polynomial for log(1 - w) near the axis, else
+  // the log of the better-conditioned of 1 - w and u (one log either way)
+  float lw = log1m_poly4(w4);
+  float lu = flog(fsel(w4 <= 2.0f, fmaf(w4, -0.25f, 1.0f), u));
+  r.L = fsel(w4 < 0.25f, lw, lu);
   r.u = u;
-  r.w = w;
+  r.w = 0.25f * w4;
   r.X = fmaf(vx, L.xx, fmaf(vy, L.xy, vz * L.xz));
   r.Y = fmaf(vx, yx, fmaf(vy, yy, vz * yz));
   r.S = fmaf(r.X, r.X, r.Y * r.Y);
@@ -497,7 +498,7 @@ __device__ __forceinline__ void backward_lobe(const Lobe& L, const LobeAux& A, c
   float g_cp = fmaf(vx, gP, vy * gQ);
   float g_sp = fmaf(vy, gP, -vx * gQ);
   // theta: ct = tanh(o0/2), st = sech(o0/2): dct/do0 = st^2/2, dst/do0 = -st ct/2
-  g[0] = 0.5f * A.st * fmaf(A.st, g_ct, -A.ct * g_st);
+  g[0] = A.hst * fmaf(A.st, g_ct, -A.ct * g_st);
   // (cp, sp) = (d2, d1)/n: d/d d1 = cp t, d/d d2 = -sp t with t = (cp g_sp - sp g_cp)/n
   float tp = fmaf(A.cp, g_sp, -A.sp * g_cp) * A.inv_np;
   float tt = fmaf(A.ctau, g_stau, -A.stau * g_ctau) * A.inv_nt;
