@@ -18,7 +18,7 @@ REC_TILE = 64
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _rows(t, rows, name, device=None):
@@ -28,12 +28,14 @@ def _rows(t, rows, name, device=None):
         raise TypeError(f"{name} must be a float32 CUDA tensor")
     if device is not None and t.device != device:
         raise ValueError(f"{name} is on {t.device}, the guide on {device}")
-    if t.dim() != 2 or t.shape[0] != rows or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or shape[0] != rows or (shape[1] > 1 and stride[1] != 1):
         raise ValueError(f"{name} must be [{rows}, B] with unit stride along B")
-    ld = t.stride(0) if rows > 1 else max(t.shape[1], 1)
-    if ld < t.shape[1]:
-        raise ValueError(f"{name}: rows overlap (leading dimension {ld} < B = {t.shape[1]})")
-    return t.shape[1], ld
+    B = shape[1]
+    ld = stride[0] if rows > 1 else max(B, 1)
+    if ld < B:
+        raise ValueError(f"{name}: rows overlap (leading dimension {ld} < B = {B})")
+    return B, ld
 
 
 def _out_rows(t, rows, B, ld, name, device):
@@ -41,10 +43,11 @@ def _out_rows(t, rows, B, ld, name, device):
     0..B-1 of each row at row * ld, so its rows must have the input's stride."""
     if not isinstance(t, torch.Tensor) or t.dtype != torch.float32 or not t.is_cuda or t.device != device:
         raise TypeError(f"{name} must be a float32 tensor on {device}")
-    if t.dim() != 2 or t.shape[0] != rows or t.shape[1] < B or (t.shape[1] > 1 and t.stride(1) != 1):
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or shape[0] != rows or shape[1] < B or (shape[1] > 1 and stride[1] != 1):
         raise ValueError(f"{name} must be [{rows}, >= {B}] with unit stride along B")
-    if rows > 1 and t.stride(0) != ld:
-        raise ValueError(f"{name} must have leading dimension {ld} (the input's), not {t.stride(0)}")
+    if rows > 1 and stride[0] != ld:
+        raise ValueError(f"{name} must have leading dimension {ld} (the input's), not {stride[0]}")
 
 
 def _vec(t, n, name, device):
@@ -114,7 +117,9 @@ class NasgGuide:
     # -- plumbing ------------------------------------------------------------
     @staticmethod
     def _stream():
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the current device's current stream, without building a Stream object
+        # around it (2 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
     def close(self):
         if getattr(self, "_ctx", None) is not None and self._ctx.value:
@@ -212,8 +217,8 @@ class NasgGuide:
         check(self.lib.nasg_query(self._ctx, _ptr(feat), _ptr(xi), ld, B, _ptr(dir_out), _ptr(pdf_out),
                                   _ptr(sel_out), _ptr(rec_out), self._stream()))
         if rec_out is not None:
-            return dir_out[:, :B], pdf_out[:B], rec_out
-        return dir_out[:, :B], pdf_out[:B]
+            return dir_out.narrow(1, 0, B), pdf_out.narrow(0, 0, B), rec_out
+        return dir_out.narrow(1, 0, B), pdf_out.narrow(0, 0, B)
 
     def pdf(self, rec, dirs, pdf_out=None):
         dev = self.device
@@ -224,7 +229,7 @@ class NasgGuide:
         else:
             _vec(pdf_out, B, "pdf_out", dev)
         check(self.lib.nasg_pdf(self._ctx, _ptr(rec), _ptr(dirs), ld, B, _ptr(pdf_out), self._stream()))
-        return pdf_out[:B]
+        return pdf_out.narrow(0, 0, B)
 
     def pdf_grad(self, rec, dirs, pdf_out=None, grad_out=None):
         """(pdf [B], gradient of log pdf on the sphere [3, B]) at dirs."""
@@ -241,7 +246,7 @@ class NasgGuide:
             _out_rows(grad_out, 3, B, ld, "grad_out", dev)
         check(self.lib.nasg_pdf_grad(self._ctx, _ptr(rec), _ptr(dirs), ld, B, _ptr(pdf_out), _ptr(grad_out),
                                      self._stream()))
-        return pdf_out[:B], grad_out[:, :B]
+        return pdf_out.narrow(0, 0, B), grad_out.narrow(1, 0, B)
 
     def sample(self, rec, xi, dir_out=None, pdf_out=None):
         dev = self.device
@@ -257,7 +262,7 @@ class NasgGuide:
             _vec(pdf_out, B, "pdf_out", dev)
         check(self.lib.nasg_sample(self._ctx, _ptr(rec), _ptr(xi), ld, B, _ptr(dir_out), _ptr(pdf_out),
                                    self._stream()))
-        return dir_out[:, :B], pdf_out[:B]
+        return dir_out.narrow(1, 0, B), pdf_out.narrow(0, 0, B)
 
     def _train_args(self, feat, dirs, w, bsdf_pdf):
         dev = self.device
