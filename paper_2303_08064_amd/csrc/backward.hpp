@@ -209,14 +209,14 @@ __device__ __forceinline__ void stage_input_bf16(void* buf, const EncodedInput& 
 }
 
 // Write a wave's accumulator-layout block [RT*16 rows][16 vertices] into the
-// FP32 staging buffer [row][vertex] at vertex column wave*16.
+// FP32 staging buffer [row][vertex] at vertex columns wave*16 .. (stage_col_f32).
 template <int RT, int SP>
 __device__ __forceinline__ void stage_rows_f32(float* buf, const float (&x)[RT][4], int wave, int lane) {
-  const int g = lane >> 4, c = lane & 15;
+  const int g = lane >> 4, col = wave * 16 + stage_col_f32(lane & 15);
 #pragma unroll
   for (int mt = 0; mt < RT; ++mt)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) buf[(mt * 16 + 4 * g + i) * SP + wave * 16 + c] = x[mt][i];
+    for (int i = 0; i < 4; ++i) buf[(mt * 16 + 4 * g + i) * SP + col] = x[mt][i];
 }
 
 // BF16 rows of a block packed in pairs (as the MFMA operands hold them):
@@ -303,7 +303,7 @@ template <int SP, int NR, int NC, int NV = kWGV>
 __device__ __forceinline__ void wgrad_tiles_f32(const float* dst, const float* hst, const int (&rt)[NR], int nrt,
                                                 f32x4 (&acc)[NR][NC], int lane) {
   const int g = lane >> 4, c = lane & 15;
-  // lane group g takes vertices vb*16 + 4g .. + 3, one 16-byte read per row
+  // lane group g takes columns vb*16 + 4g .. + 3, one 16-byte read per row
 #pragma unroll
   for (int vb = 0; vb < NV / 16; ++vb) {
     f32x4 hb[NC];

@@ -108,6 +108,12 @@ __device__ __forceinline__ uint32_t relu_indicator(uint32_t h) {
   return ind;
 }
 
+// Column of vertex c of 16 in an FP32 staging buffer: lane group g's 16-byte
+// read of columns 4g .. 4g + 3 then holds vertices g, 4 + g, 8 + g, 12 + g, so
+// that the MFMA over its i-th elements sums vertices 4i .. 4i + 3 and the
+// sixteen are summed in their order.
+__device__ __forceinline__ int stage_col_f32(int c) { return 4 * (c & 3) + (c >> 2); }
+
 // The FP32 counterpart for MT row tiles and KQ 16-wide contraction blocks:
 // acc[mt] = sum over kq, i of A(mt, kq)[i] b(kq, i), chained in that order,
 // A(mt, kq) being the lane's four operands of block kq (one 16-byte LDS read).

@@ -347,10 +347,10 @@ struct Mlp<H, K, 0, E> {
   // padding
   template <int SP>
   __device__ __forceinline__ static void stage_input(float* st, const Input& x, int wave, int lane) {
-    const int g = lane >> 4, c = lane & 15;
+    const int g = lane >> 4, col = wave * 16 + stage_col_f32(lane & 15);
 #pragma unroll
-    for (int kb = 0; kb < KB0; ++kb) st[(kb * 4 + g) * SP + wave * 16 + c] = x.x[kb];
-    if constexpr (E == 0) st[(12 + g) * SP + wave * 16 + c] = 0.0f;
+    for (int kb = 0; kb < KB0; ++kb) st[(kb * 4 + g) * SP + col] = x.x[kb];
+    if constexpr (E == 0) st[(12 + g) * SP + col] = 0.0f;
   }
 
   __device__ __forceinline__ static void layer0(const float* lds, const Input& x, float (&h)[MTH][4], int lane) {

@@ -122,7 +122,16 @@ void train_kernel(TrainArgs a) {
   for (int j = 0; j < C::OO::TPW; ++j) acco[j] = zero4();
   double loss_sum = 0.0, w_sum = 0.0;
 
-  const int64_t n_tiles = (a.B + NV - 1) / NV;
+  // FP32 with eight waves: a workgroup's 128 vertices are two of the
+  // 64-vertex tiles that it would run with four (blockIdx.x + gridDim.x j), in
+  // their order, so that both sum a workgroup's gradient alike, bit for bit
+  constexpr bool PAIRED = PREC == 0 && NW == 8;
+  constexpr int TV = PAIRED ? kWGV : NV;
+  const int64_t n_tiles = (a.B + TV - 1) / TV;
+  const int64_t step = PAIRED ? 2 * gridDim.x : gridDim.x;
+  auto vertex = [&](int64_t tile) {
+    return PAIRED ? (tile + (wave >> 2) * gridDim.x) * TV + (wave & 3) * 16 + c : tile * TV + wave * 16 + c;
+  };
   // this vertex's inputs, loaded one tile ahead so that their latency
   // overlaps the previous tile's work: without branches (padding lanes read
   // the batch's last vertex) and converted only when their tile starts, or
@@ -132,8 +141,9 @@ void train_kernel(TrainArgs a) {
     typename M::Raw x;
     float dx, dy, dz, w, pfs;
   };
-  auto load_in = [&](int64_t vv) {
+  auto load_in = [&](int64_t tile) {
     In r;
+    int64_t vv = vertex(tile);
     vv = vv < a.B ? vv : a.B - 1;
     r.x = M::load_raw(a.feat, a.ld, vv, g);
     r.dx = a.dir[vv]; r.dy = a.dir[a.ld + vv]; r.dz = a.dir[2 * a.ld + vv];
@@ -141,14 +151,13 @@ void train_kernel(TrainArgs a) {
     r.pfs = SEL == 1 ? a.bsdf_pdf[vv] : 0.0f;
     return r;
   };
-  In nxt = load_in((int64_t)blockIdx.x * NV + wave * 16 + c);   // in flight beside the weights
+  In nxt = load_in(blockIdx.x);   // in flight beside the weights
   lds_dma_wait();
   __syncthreads();
-  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const int64_t v = tile * NV + wave * 16 + c;
-    const bool valid = v < a.B;
+  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += step) {
+    const bool valid = vertex(tile) < a.B;
     const In cur = nxt;
-    if (tile + gridDim.x < n_tiles) nxt = load_in((tile + gridDim.x) * NV + wave * 16 + c);
+    if (tile + step < n_tiles) nxt = load_in(tile + step);
     // ---- forward (recomputed) ----
     const typename M::Input x = M::input(cur.x, valid, g);
     // BF16 keeps the activations packed (hw, lastw), FP32 as floats (h, last)
@@ -293,18 +302,23 @@ int train_workgroups(int64_t B, int num_cus) {
 // 64-vertex tiles would fill every CU, four over 64 below (twice the CUs, one
 // wave per SIMD); the smaller BF16 networks, whose tiles are short beside the
 // sum over the workgroups' gradients, from half the CUs on. FP32 with K = 16:
-// always four (its weights and the staging of 128 vertices exceed the LDS).
+// always four (its weights and the staging of 128 vertices exceed the LDS);
+// FP32 with K = 8 also where 64-vertex tiles make three rounds over the CUs,
+// of which eight waves would run the fourth as well (40000 samples: four 67.6,
+// eight 72.7 us; K = 4 53.0 and 51.4).
 // Measured (us per step, four / eight waves): FP32 K = 8 4096 samples 32.2 /
 // 41.7, 16384 36.9 / 45.5, 20000 53.2 / 46.5, 2^18 288 / 246; BF16 K = 16 4096
 // 24.1 / 24.5, 16384 28.1 / 29.5, 20000 35.6 / 30.7, 2^18 148 / 105; K = 4
 // 4096 17.8 / 17.9, 16384 23.0 / 20.2.
 static bool train_is_wide(int64_t B, int num_cus, int K, int prec) {
   const int64_t tiles = (B + kWGV - 1) / kWGV;
-  return prec == 1 ? (K == 16 ? tiles : 2 * tiles) > num_cus : K < 16 && tiles > num_cus;
+  if (prec == 1) return (K == 16 ? tiles : 2 * tiles) > num_cus;
+  const int64_t rounds = (tiles + num_cus - 1) / num_cus;
+  return K < 16 && rounds > 1 && (K < 8 || rounds != 3);
 }
 
 int small_train_workgroups(int64_t B, int num_cus, int K, int prec) {
-  return train_workgroups(train_is_wide(B, num_cus, K, prec) ? (B + 1) / 2 : B, num_cus);
+  return train_workgroups(prec == 1 && train_is_wide(B, num_cus, K, prec) ? (B + 1) / 2 : B, num_cus);
 }
 
 template <int H, int K, int PREC, int SEL, int NW>
