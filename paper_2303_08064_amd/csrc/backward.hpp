@@ -61,14 +61,15 @@ __device__ __forceinline__ void dgrad(const void* wl, const float (&dl)[RT][4],
   } else {
     // slot (kb, g) is row (kb/4)*16 + 4g + kb%4 of layer l: accumulator
     // dl[kb/4][kb%4] of this lane
-    constexpr int P = f32_pitch(H);
     const int g = lane >> 4, c = lane & 15;
-    const float* W = reinterpret_cast<const float*>(wl) + 4 * g * P + c;
+    const float* W[4];   // row 4g, by (mt ^ i) % 4: row 4g + i's column 16 mt + c but for constants
+#pragma unroll
+    for (int j = 0; j < 4; ++j) W[j] = reinterpret_cast<const float*>(wl) + f32_row(4 * g, H) + 16 * (j ^ g) + c;
     f32x4 acc[MTP];
     mfma_rows_f32<MTP, RT>(
         [&](int mt, int kq) {
-          const float* w = W + kq * 16 * P + mt * 16;
-          return f32x4{w[0], w[P], w[2 * P], w[3 * P]};
+          auto at = [&](int i) { return W[(mt ^ i) & 3][f32_rows(kq * 16, H) + f32_row(i, H) + (mt & ~3) * 16]; };
+          return f32x4{at(0), at(1), at(2), at(3)};
         },
         [&](int kq, int i) { return dl[kq][i]; }, acc);
 #pragma unroll

@@ -346,9 +346,8 @@ struct NetF32 {
   static constexpr int MTH = H / 16, MTO = K / 2 + SEL, KQ = K / 4;
   static constexpr int CH = 64;              // rows per LDS chunk
   static constexpr int TPC = CH / 16;        // row tiles per chunk
-  static constexpr int PH = f32_pitch(H);    // pitch of hidden and output layers
   static constexpr int P0 = M::IN + 1;       // pitch of layer 0
-  static constexpr int BUF = (CH * PH > H * P0) ? CH * PH : H * P0;
+  static constexpr int BUF = f32_rows(CH, H) > H * P0 ? f32_rows(CH, H) : H * P0;
   static constexpr int SP = kWGV + 4;
   // rows of the backward's delta staging: the output layer's or a hidden layer's
   static constexpr int RMAX = (8 * K + 16 * SEL > H) ? 8 * K + 16 * SEL : H;
@@ -370,7 +369,7 @@ struct NetF32 {
     constexpr int NCH = MT_ / TPC, TAIL = MT_ % TPC;
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
-      wstage(buf, wg + Lt.off(l) + (int64_t)ch * CH * PH, CH * PH);
+      wstage(buf, wg + Lt.off(l) + f32_rows(ch * CH, H), f32_rows(CH, H));
       float part[TPC][4];
       M::template gemm<TPC>(buf, in, part, lane);   // rows ch*CH .. ch*CH + CH - 1
 #pragma unroll
@@ -379,7 +378,7 @@ struct NetF32 {
         for (int i = 0; i < 4; ++i) y[ch * TPC + t][i] = part[t][i];
     }
     if constexpr (TAIL > 0) {
-      wstage(buf, wg + Lt.off(l) + (int64_t)NCH * CH * PH, TAIL * 16 * PH);
+      wstage(buf, wg + Lt.off(l) + f32_rows(NCH * CH, H), f32_rows(TAIL * 16, H));
       float part[TAIL][4];
       M::template gemm<TAIL>(buf, in, part, lane);
 #pragma unroll
@@ -421,21 +420,25 @@ struct NetF32 {
     const F32Layout Lt = layout();
     const int g = lane >> 4, c = lane & 15;
     constexpr int NCH = (RT + TPC - 1) / TPC;
+    const W* w[4];   // row 4g of a chunk, by (mt ^ i) % 4 (F32Layout)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = buf + f32_row(4 * g, H) + 16 * (j ^ g) + c;
     f32x4 acc[MTH];
 #pragma unroll
     for (int mt = 0; mt < MTH; ++mt) acc[mt] = zero4();
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
       const int nt = (ch + 1) * TPC <= RT ? TPC : RT - ch * TPC;   // row tiles in this chunk
-      wstage(buf, wg + Lt.off(l) + (int64_t)ch * CH * PH, nt * 16 * PH);
+      wstage(buf, wg + Lt.off(l) + f32_rows(ch * CH, H), f32_rows(nt * 16, H));
 #pragma unroll
       for (int mt = 0; mt < MTH; ++mt)
 #pragma unroll
         for (int kk = 0; kk < 4 * TPC; ++kk) {
           if (kk < 4 * nt) {
             const int kb = 4 * TPC * ch + kk;
-            const int r = ((kb >> 2) - TPC * ch) * 16 + 4 * g + (kb & 3);
-            acc[mt] = mfma_f32_4(buf[r * PH + mt * 16 + c], dl[kb >> 2][kb & 3], acc[mt]);
+            const int i = kb & 3;   // row ((kb >> 2) - TPC * ch) * 16 + 4g + i of the chunk
+            const int at = f32_rows(((kb >> 2) - TPC * ch) * 16, H) + f32_row(i, H) + (mt & ~3) * 16;
+            acc[mt] = mfma_f32_4(w[(mt ^ i) & 3][at], dl[kb >> 2][i], acc[mt]);
           }
         }
     }

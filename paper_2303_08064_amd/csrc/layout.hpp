@@ -106,23 +106,25 @@ struct Bf16Layout {
   NASG_HD int64_t total_elems() const { return bwd_sel_off() + (int64_t)16 * d.S * d.H; }
 };
 
-// pitch of the FP32 hidden and output layers
-NASG_HD constexpr int f32_pitch(int H) { return H + 4; }
-
 // ---- FP32 row-major layout (elements are float) ----
-// layer l: [rows][pitch], pitch 16 + 1 or 64 + 1 (l == 0) or H + 4; output
-// rows in physical order. H + 4 keeps rows 16-byte aligned, and its reads are
-// free of LDS bank conflicts both ways: the forward's 16-byte reads (lane
-// (g, c): row c, columns 4g ..: 16 lanes c cover the 64 banks) and the
-// backward's 4-byte ones (row 4g, column c: bank 16g + c).
+// layer 0: [rows][16 + 1 or 64 + 1]; the others in groups of four rows of H
+// and four floats of padding; output rows in physical order. The groups keep
+// every row 16-byte aligned, and column k of row r is kept at k ^ 16 x, x =
+// (r ^ r/4) % 4. The 16 rows of a forward read (16 bytes: row c, columns
+// 16 kq + 4g ..) then cover the 64 banks, and a backward read (4 bytes: row
+// 4g + i, column 16 mt + c) meets in a bank twice at most.
+NASG_HD constexpr int f32_rows(int rows, int H) { return rows * (H + 1); }   // floats of a multiple of four rows
+NASG_HD constexpr int f32_row(int r, int H) { return r * H + 4 * (r >> 2); }  // first float of row r
+NASG_HD constexpr int f32_col(int r, int k) { return k ^ (16 * ((r ^ (r >> 2)) & 3)); }   // column k's place in row r
+
 struct F32Layout {
   NetDims d;
-  NASG_HD int pitch(int l) const { return l == 0 ? d.in_pad() + 1 : f32_pitch(d.H); }
+  NASG_HD int pitch0() const { return d.in_pad() + 1; }
   NASG_HD int64_t off(int l) const {
     if (l == 0) return 0;
-    return (int64_t)d.H * pitch(0) + (int64_t)(l - 1) * d.H * pitch(1);
+    return (int64_t)d.H * pitch0() + (int64_t)(l - 1) * f32_rows(d.H, d.H);
   }
-  NASG_HD int64_t total_elems() const { return off(d.NH) + (int64_t)d.out_rows() * pitch(d.NH); }
+  NASG_HD int64_t total_elems() const { return off(d.NH) + f32_rows(d.out_rows(), d.H); }
 };
 
 }  // namespace nasg
@@ -163,7 +165,8 @@ NASG_HD int64_t bf16_bwd_pos(const Bf16Layout& Lt, int l, int n, int k) {
 
 NASG_HD int64_t f32_pos(const F32Layout& Lt, int l, int n, int k) {
   int R = (l == Lt.d.NH) ? inv_canon_out_row(n, Lt.d.K) : n;
-  return Lt.off(l) + (int64_t)R * Lt.pitch(l) + k;
+  if (l == 0) return (int64_t)R * Lt.pitch0() + k;
+  return Lt.off(l) + f32_row(R, Lt.d.H) + f32_col(R, k);
 }
 
 // Gather form: canonical (l, n, k) of packed element e, or k = -1 for padding.
@@ -219,12 +222,19 @@ NASG_HD void f32_source(const F32Layout& Lt, int64_t e, int& l, int& n, int& k) 
   if (e < Lt.off(1)) {
     l = 0;
   } else {
-    l = 1 + (int)((e - Lt.off(1)) / ((int64_t)d.H * Lt.pitch(1)));
+    l = 1 + (int)((e - Lt.off(1)) / f32_rows(d.H, d.H));
     if (l > d.NH) l = d.NH;
   }
-  int64_t el = e - Lt.off(l);
-  int R = (int)(el / Lt.pitch(l));
-  k = (int)(el % Lt.pitch(l));
+  const int el = (int)(e - Lt.off(l));
+  int R;
+  if (l == 0) {
+    R = el / Lt.pitch0();
+    k = el % Lt.pitch0();
+  } else {
+    const int group = f32_rows(4, d.H), in = el % group;
+    R = 4 * (el / group) + in / d.H;
+    k = in < 4 * d.H ? f32_col(R, in % d.H) : d.cols(l);   // else padding
+  }
   n = (l == d.NH) ? canon_out_row(R, d.K) : R;
   if (k >= d.cols(l) || n < 0) k = -1;
 }

@@ -366,16 +366,17 @@ struct Mlp<H, K, 0, E> {
     }
   }
 
-  // out = W in; W row-major [MT*16][pitch] at `lds`, input neuron of slot
+  // out = W in; W's MT*16 rows (F32Layout) at `lds`, input neuron of slot
   // (kb, g) is (kb/4)*16 + 4g + kb%4 = accumulator in[kb/4][kb%4] of this lane
   template <int MT>
   __device__ __forceinline__ static void gemm(const float* lds, const float (&in)[MTH][4], float (&out)[MT][4], int lane) {
     const int g = lane >> 4, c = lane & 15;
-    constexpr int P = f32_pitch(H);
-    const float* row = lds + c * P + 4 * g;
+    const float* row[4];   // row c's 16-column blocks kq % 4
+#pragma unroll
+    for (int j = 0; j < 4; ++j) row[j] = lds + f32_row(c, H) + f32_col(c, 16 * j) + 4 * g;
     f32x4 acc[MT];
     mfma_rows_f32<MT, MTH>(
-        [&](int mt, int kq) { return *reinterpret_cast<const f32x4*>(row + mt * 16 * P + kq * 16); },
+        [&](int mt, int kq) { return *reinterpret_cast<const f32x4*>(row[kq & 3] + f32_rows(mt * 16, H) + (kq & ~3) * 16); },
         [&](int kq, int i) { return in[kq][i]; }, acc);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
