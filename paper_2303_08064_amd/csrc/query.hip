@@ -5,7 +5,7 @@
 // Lane (g, c) of a wave owns vertex c of a 16-vertex block and lobes
 // g*K/4 .. g*K/4 + K/4 - 1 of that vertex, so reductions over lobes are a
 // within-lane loop plus two cross-lane steps (xor 16, xor 32). A wave takes
-// one block per pass, four (one sample per lane: query_four_blocks) or two
+// one block per pass, four (one sample per lane) or two
 // (the paper's network), with the multi-block passes' inputs staged in LDS
 // one pass ahead.
 #include <type_traits>
@@ -296,8 +296,13 @@ static QueryKernel find_query_kernel(const NetDims& d, int prec, int mode, bool 
 // Measured (us, one-block / four-block): K = 16 BF16 777 vertices 5.7 / 13.8,
 // 65536 13.0 / 14.7, 131072 22.2 / 20.1, 300000 55 / 43; K = 8 FP32 777
 // 8.5 / 41, 98304 34.1 / 42.6, 131072 44.1 / 42.6, 200000 71 / 82.
-static bool query_is_small(int64_t B, int num_cus, int prec) {
+// BF16 with K = 4 and 8, which hold three one-block waves per SIMD: one block
+// up to seven rounds. K = 8 50000 8.7 / 10.7, 65536 8.9 / 11.0, 100000 12.7 /
+// 13.9, 131072 13.6 / 14.0, 180000 18.3 / 18.8, 250000 28.7 / 25.9; K = 4
+// 65536 6.9 / 8.5, 100000 9.0 / 10.3, 131072 10.6 / 10.4, 180000 13.0 / 13.0.
+static bool query_is_small(int64_t B, int num_cus, int K, int prec) {
   const int64_t wave = 8LL * num_cus;
+  if (prec == 1 && K < 16) return B <= 7 * 16 * wave;
   const int64_t full1 = B / (16 * wave), rest1 = B - full1 * 16 * wave;
   const int64_t full4 = B / (64 * wave), rest4 = B - full4 * 64 * wave;
   const int64_t one = prec == 1 ? 29 : 27;
@@ -307,7 +312,7 @@ static bool query_is_small(int64_t B, int num_cus, int prec) {
 }
 
 hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode, hipStream_t st) {
-  const bool small = query_is_small(a.B, a.num_cus, prec);
+  const bool small = query_is_small(a.B, a.num_cus, d.K, prec);
   const QueryKernel k = find_query_kernel(d, prec, mode, small);
   if (k.nb == 0) return hipErrorInvalidValue;
   const int TV = kTileV * k.nb;   // vertices per wave pass

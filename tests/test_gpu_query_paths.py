@@ -13,14 +13,14 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("name", ["c1_bf16", "c2_bf16", "c3_bf16", "c3s_bf16", "c1_f32", "c2_f32", "c2s_f32", "c3_f32"])
 def test_one_and_four_block_passes_agree_bitwise(name):
-    """A batch of one full round of four-block passes less a ragged end (inside
+    """A batch of two full rounds of four-block passes less a ragged end (inside
     a block) against its vertices queried in batches of one-block passes: the
     first, a middle and the last ones, in batches that end inside a block, fill
     it, and hold a single vertex."""
     K = CONFIGS[name][2]
     g, _ = make_guide(name, out_scale=8.0)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    full = 512 * cus - 37
+    full = 1024 * cus - 37
     rng = synth.rng_for(77)
     feat, xi = to_dev(synth.features(full, rng)), to_dev(synth.uniforms(full, rng))
     sel = torch.empty(full, device="cuda") if g.selection else None
