@@ -293,16 +293,17 @@ static QueryKernel find_query_kernel(const NetDims& d, int prec, int mode, bool 
 // of at most half the waves (one per SIMD) 15. A last four-block round of at most half the waves
 // takes 58 in BF16; in FP32, whose chains of 32-cycle MFMAs wait for
 // themselves, as long as a full one.
-// Measured (us, one-block / four-block): K = 16 BF16 777 vertices 5.7 / 13.8,
-// 65536 13.0 / 14.7, 131072 22.2 / 20.1, 300000 55 / 43; K = 8 FP32 777
-// 8.5 / 41, 98304 34.1 / 42.6, 131072 44.1 / 42.6, 200000 71 / 82.
+// Measured (us, one-block / four-block): K = 16 BF16 777 vertices 5.5 / 13.5,
+// 65536 12.6 / 14.7, 131072 22.0 / 20.9, 300000 46.5 / 43.4; K = 8 FP32 777
+// 8.7 / 41, 98304 35.3 / 43.0, 131072 45.1 / 43.4, 200000 71 / 83.
 // BF16 with K = 4 and 8, which hold three one-block waves per SIMD: one block
-// up to seven rounds. K = 8 50000 8.7 / 10.7, 65536 8.9 / 11.0, 100000 12.7 /
-// 13.9, 131072 13.6 / 14.0, 180000 18.3 / 18.8, 250000 28.7 / 25.9; K = 4
-// 65536 6.9 / 8.5, 100000 9.0 / 10.3, 131072 10.6 / 10.4, 180000 13.0 / 13.0.
+// up to six and seven rounds. K = 8 50000 8.3 / 10.4, 65536 8.6 / 10.6, 100000
+// 12.9 / 14.1, 131072 14.2 / 14.2, 180000 18.9 / 19.3, 229000 24.1 / 25.9,
+// 262144 27.1 / 26.1; K = 4 65536 6.9 / 8.5, 100000 9.1 / 10.4, 180000 13.4 /
+// 13.4, 229000 17.3 / 15.9.
 static bool query_is_small(int64_t B, int num_cus, int K, int prec) {
   const int64_t wave = 8LL * num_cus;
-  if (prec == 1 && K < 16) return B <= 7 * 16 * wave;
+  if (prec == 1 && K < 16) return B <= (K == 4 ? 6 : 7) * 16 * wave;
   const int64_t full1 = B / (16 * wave), rest1 = B - full1 * 16 * wave;
   const int64_t full4 = B / (64 * wave), rest4 = B - full4 * 64 * wave;
   const int64_t one = prec == 1 ? 29 : 27;

@@ -304,12 +304,12 @@ int train_workgroups(int64_t B, int num_cus) {
 // sum over the workgroups' gradients, from half the CUs on. FP32 with K = 16:
 // always four (its weights and the staging of 128 vertices exceed the LDS);
 // FP32 with K = 8 also where 64-vertex tiles make three rounds over the CUs,
-// of which eight waves would run the fourth as well (40000 samples: four 67.6,
-// eight 72.7 us; K = 4 53.0 and 51.4).
-// Measured (us per step, four / eight waves): FP32 K = 8 4096 samples 32.2 /
-// 41.7, 16384 36.9 / 45.5, 20000 53.2 / 46.5, 2^18 288 / 246; BF16 K = 16 4096
-// 24.1 / 24.5, 16384 28.1 / 29.5, 20000 35.6 / 30.7, 2^18 148 / 105; K = 4
-// 4096 17.8 / 17.9, 16384 23.0 / 20.2.
+// of which eight waves would run the fourth as well.
+// Measured (us per step, four / eight waves): FP32 K = 8 4096 samples 28.6 /
+// 40.3, 16384 33.7 / 45.1, 20000 48.8 / 45.1, 40000 64.1 / 71.9, 2^18 273 / 245;
+// K = 4 40000 51.0 / 51.5, 2^18 205 / 162; BF16 K = 16 4096 20.2 / 22.2, 16384
+// 23.9 / 26.6, 20000 29.1 / 27.3, 2^18 110 / 95; K = 4 4096 14.4 / 15.6, 16384
+// 18.9 / 17.8.
 static bool train_is_wide(int64_t B, int num_cus, int K, int prec) {
   const int64_t tiles = (B + kWGV - 1) / kWGV;
   if (prec == 1) return (K == 16 ? tiles : 2 * tiles) > num_cus;
