@@ -155,6 +155,13 @@ __device__ __forceinline__ float query_decode(const float (&out)[MTO][4], float 
   inv_se = frcp(se);
 #pragma unroll
   for (int q = 0; q < KQ; ++q) lb[q].c *= ea[q] * inv_se;
+  // where the rounding of logits beyond about 1e9 overflows the sum, the
+  // log-sum-exp is +infinity, every log c_k of the records -infinity and the
+  // density 0; here 0 times infinity
+  if (__any(se == INFINITY)) {
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) lb[q].c = fsel(se == INFINITY, 0.0f, lb[q].c);
+  }
   return mx + flog(se);
 }
 
@@ -179,7 +186,12 @@ __device__ __forceinline__ float query_pdf(const QueryLobe (&lb)[KQ], float vx, 
 #pragma clang fp contract(off)
   float s = 0.0f;
 #pragma unroll
-  for (int q = 0; q < KQ; ++q) s = fmaf(lb[q].c, eval_query_lobe(lb[q], vx, vy, vz, eps), s);
+  for (int q = 0; q < KQ; ++q) {
+    bool on;
+    const float lg = eval_query_lobe(lb[q], vx, vy, vz, eps, on);
+    // a lobe without density adds nothing, whatever its weight (NaN among them)
+    s = fsel(on, fmaf(lb[q].c, __builtin_amdgcn_exp2f(lg), s), s);
+  }
   return quad_sum(s) * query_pdf_scale(eps);
 }
 

@@ -340,14 +340,17 @@ __device__ __forceinline__ Eval eval_lobe(const Lobe& L, float vx, float vy, flo
   return r;
 }
 
-// G(v) of a query lobe at a unit direction (eq. NASG; App. A with epsilon):
-// the same function as eval_lobe without the lobe's y axis. For a unit v and
+// log2 G(v) of a query lobe at a unit direction (eq. NASG; App. A with
+// epsilon): the same function as eval_lobe without the lobe's y axis. `on` is
+// whether G > 0: not at v = -z (u = 0) and, as in eval_lobe, not where the
+// frame or the direction is NaN. For a unit v and
 // an orthonormal frame X^2 + Y^2 = 1 - (v.z)^2 = (1 - v.z)(1 + v.z) =
 // 4 (1 - u) u, a product of the two cancellation-free terms already at hand;
 // c^2 is capped at 1 against rounding (X^2 and 4 u (1 - u) come from
 // different roundings), which also makes 0 / 0 at v = z into 1 (log u = 0
 // there, whatever c^2 is).
-__device__ __forceinline__ float eval_query_lobe(const QueryLobe& q, float vx, float vy, float vz, float eps) {
+__device__ __forceinline__ float eval_query_lobe(const QueryLobe& q, float vx, float vy, float vz, float eps,
+                                                 bool& on) {
 #pragma clang fp contract(off)
   const float dx = vx - q.zx, dy = vy - q.zy, dz = vz - q.zz;
   const float sx = vx + q.zx, sy = vy + q.zy, sz = vz + q.zz;
@@ -362,8 +365,8 @@ __device__ __forceinline__ float eval_query_lobe(const QueryLobe& q, float vx, f
   const float X = fmaf(dx, q.xx, fmaf(dy, q.xy, dz * q.xz));
   const float c2 = fminf(X * X * frcp(w4 * u), 1.0f);
   const float pm1 = fmaf(q.a, c2, eps);                     // p - 1 without cancellation
-  const float lg = fmaf(q.lam, exp2m1_neg(fmaf(pm1, Lu, Lu), Const2Log2e()), pm1 * Lu);   // log2 G
-  return fsel(u > 0.0f, __builtin_amdgcn_exp2f(lg), 0.0f);  // G(-z) = 0
+  on = u > 0.0f;
+  return fmaf(q.lam, exp2m1_neg(fmaf(pm1, Lu, Lu), Const2Log2e()), pm1 * Lu);
 }
 // the mixture pdf over sum_k c_k G_k: sqrt(1 + eps) / (2 pi)
 __device__ __forceinline__ float query_pdf_scale(float eps) { return fsqrt(1.0f + eps) * 0.159154943091895336f; }
