@@ -134,14 +134,15 @@ struct LobeAux {
   float omq;                // 1 - 2 lam / expm1(2 lam) = -d log K / d log lam
 };
 
-// A (cos, sin) pair divided by its norm; a zero pair becomes (1, 0).
+// A (cos, sin) pair divided by its norm; a zero pair and one with a NaN become
+// (1, 0).
 __device__ __forceinline__ void unit_pair(float c, float s, float& cu, float& su, float& inv) {
   float n2 = fmaf(c, c, s * s);
   inv = frsq(n2);
   bool ok = n2 > 0.0f;
-  inv = fsel(ok, inv, 0.0f);
   cu = fsel(ok, c * inv, 1.0f);
-  su = s * inv;
+  su = fsel(ok, s * inv, 0.0f);
+  inv = fsel(ok, inv, 0.0f);
 }
 
 // log(2 pi) + log(one_m) - loglam - (1/2) log((1+eps)(1+eps+a)), the two

@@ -35,3 +35,35 @@ def test_extreme_features(name, B):
     assert np.array_equal(np.isnan(p), np.isnan(q)), (p, q)
     assert np.array_equal(p == 0, q == 0), (p, q)
     g.close()
+
+
+@pytest.mark.parametrize("name", [n for n in CONFIGS if "nh" not in n])
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+def test_nan_pair(name, p):
+    """A NaN in one raw output of a lobe's (cos, sin) pair leaves the pair
+    (1, 0), as two zeros do: the same directions, densities, records and loss
+    as with the pair's output rows zeroed. The Adam step skips its update (the
+    pair's own gradient is NaN)."""
+    K, sel = CONFIGS[name][2], "s_" in name or "paper" in name
+    rng = synth.rng_for(6)
+    feat, xi = to_dev(synth.features(1000, rng)), to_dev(synth.uniforms(1000, rng))
+    f, d, w = synth.training_batch(999, rng, synth.VmfTarget(4, seed=1001))
+    batch = [to_dev(x) for x in (f, d, w)] + ([to_dev(synth.lambert_pdf(d, f[6:9]))] if sel else [])
+    out = []
+    for value in (0.0, np.nan):
+        g, mats = make_guide(name, out_scale=8.0)
+        W = g.split(g.w)[-1]
+        first = 1 if p < 3 else 3
+        W[[first * K + 1, (first + 1) * K + 1]] = 0.0
+        W[p * K + 1] = value
+        g.repack()
+        rec = torch.zeros(((1000 + 63) // 64) * 9 * K * 64, device="cuda")
+        q = g.query(feat, xi, rec_out=rec)
+        g.train_step(*batch)
+        torch.cuda.synchronize()
+        out.append([t.clone() for t in (*q, g.stats[:2])] + [int(g.flags) & 1])
+        g.close()
+    zero, nan = out
+    for a, b in zip(zero[:4], nan[:4]):
+        assert torch.equal(a, b)
+    assert (zero[4], nan[4]) == (0, 1)
