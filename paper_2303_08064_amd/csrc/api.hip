@@ -95,8 +95,8 @@ Workspace carve(const nasg_config* c) {
   off = align_up(off + (size_t)2 * kMaxTrainWG * 2 * sizeof(double));
   w.norm_partial = off;
   off = align_up(off + (size_t)reduce_blocks(nw) * sizeof(double));
-  w.step_snapshot = off;   // then Adam's two bias corrections
-  off = align_up(off + sizeof(int64_t) + 2 * sizeof(float));
+  w.step_snapshot = off;   // then Adam's bias corrections
+  off = align_up(off + sizeof(int64_t) + sizeof(BiasCorrections));
   w.dout = off;
   if (is_large(c)) {
     // dL/d(raw outputs) of every sample of a training batch, BF16 or FP32 as the network
@@ -374,7 +374,7 @@ static nasg_status adam_only(nasg_ctx* ctx, const char* fn, unsigned char* ws, v
   a.wpack = s.wpack;
   a.step = s.step;
   a.step_snapshot = reinterpret_cast<const int64_t*>(ws + ctx->ws.step_snapshot);
-  a.corr = reinterpret_cast<const float*>(ws + ctx->ws.step_snapshot + sizeof(int64_t));
+  a.corr = reinterpret_cast<const BiasCorrections*>(ws + ctx->ws.step_snapshot + sizeof(int64_t));
   a.flags = s.flags;
   a.stats = s.stats;
   a.norm_partial = reinterpret_cast<const double*>(ws + ctx->ws.norm_partial);
@@ -386,6 +386,7 @@ static nasg_status adam_only(nasg_ctx* ctx, const char* fn, unsigned char* ws, v
   a.S = ctx->d.S;
   a.E = ctx->d.E;
   a.prec = ctx->cfg.precision;
+  a.lr = ctx->cfg.lr;
   a.beta1 = ctx->cfg.beta1;
   a.beta2 = ctx->cfg.beta2;
   a.adam_eps = ctx->cfg.adam_eps;
@@ -464,8 +465,7 @@ static nasg_status loss_grad(nasg_ctx* ctx, const char* fn, const float* feat, c
   r.stats = s.stats;
   r.step = s.step;
   r.step_snapshot = reinterpret_cast<int64_t*>(ws + ctx->ws.step_snapshot);
-  r.corr = reinterpret_cast<float*>(ws + ctx->ws.step_snapshot + sizeof(int64_t));
-  r.lr = ctx->cfg.lr;
+  r.corr = reinterpret_cast<BiasCorrections*>(ws + ctx->ws.step_snapshot + sizeof(int64_t));
   r.beta1 = ctx->cfg.beta1;
   r.beta2 = ctx->cfg.beta2;
   e = launch_reduce(r, reduce_blocks(t.n_weights), (hipStream_t)stream);

@@ -94,6 +94,12 @@ struct LargeTrainArgs {
   int num_cus;
 };
 
+// Adam's bias corrections of one step, and the betas that they are of.
+struct BiasCorrections {
+  float bc1, bc2_sqrt;   // 1 - beta1^t and sqrt(1 - beta2^t)
+  float beta1, beta2;
+};
+
 struct ReduceArgs {
   const float* partial;
   const double* loss_partial;
@@ -106,8 +112,8 @@ struct ReduceArgs {
   double* stats;
   const int64_t* step;
   int64_t* step_snapshot;
-  float* corr;           // [2] Adam's lr / (1 - beta1^t) and sqrt(1 - beta2^t) of the next step
-  float lr, beta1, beta2;
+  BiasCorrections* corr; // of the next step
+  float beta1, beta2;
 };
 
 struct AdamArgs {
@@ -118,14 +124,14 @@ struct AdamArgs {
   void* wpack;
   int64_t* step;
   const int64_t* step_snapshot;
-  const float* corr;
+  const BiasCorrections* corr;
   uint32_t* flags;
   double* stats;
   const double* norm_partial;
   int n_norm;
   int64_t n_weights;
   int H, NH, K, S, E, prec;
-  float beta1, beta2, adam_eps;
+  float lr, beta1, beta2, adam_eps;
 };
 
 // Lobe choice by inverse CDF over k = g*KQ + q (this library's reading: the

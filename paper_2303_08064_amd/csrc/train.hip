@@ -385,13 +385,16 @@ __device__ __forceinline__ double block_sum(double x, double (&red)[4]) {
   return ((red[0] + red[1]) + red[2]) + red[3];
 }
 
+// 1 - beta^t in double precision
+__device__ __forceinline__ double bias_correction(float beta, int64_t t) { return 1.0 - pow((double)beta, (double)t); }
+
 __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
   if (blockIdx.x == gridDim.x - 1) {
     __shared__ double red_l[4], red_w[4];
     // bias corrections of step t0 + 1 (used only if the step is taken)
     const int64_t t0 = *a.step;
-    if (threadIdx.x == 64) a.corr[0] = a.lr / (float)(1.0 - pow((double)a.beta1, (double)(t0 + 1)));   // lr / (1 - beta1^t)
-    if (threadIdx.x == 128) a.corr[1] = (float)sqrt(1.0 - pow((double)a.beta2, (double)(t0 + 1)));     // sqrt(1 - beta2^t)
+    if (threadIdx.x == 64) a.corr->bc1 = (float)bias_correction(a.beta1, t0 + 1);
+    if (threadIdx.x == 128) a.corr->bc2_sqrt = (float)sqrt(bias_correction(a.beta2, t0 + 1));
     double ls = 0.0, ws = 0.0;
     for (int wg = (int)threadIdx.x; wg < a.n_loss; wg += 256) {
       ls += a.loss_partial[2 * wg];
@@ -404,6 +407,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
       a.stats[1] = ws;
       a.stats[3] = ls;
       *a.step_snapshot = t0;
+      a.corr->beta1 = a.beta1;
+      a.corr->beta2 = a.beta2;
     }
     return;
   }
@@ -497,7 +502,9 @@ __device__ __forceinline__ void write_packed(const AdamArgs& a, const NetDims& d
 
 // Kingma and Ba's Adam, bias-corrected, no weight decay; skipped (weights,
 // moments and step unchanged, flag bit 0 set) if the loss or the gradient norm
-// is not finite. Bound by latency (21120 weights are 350 KB): a thread's first
+// is not finite. The corrections that reduce_kernel left are used where they
+// are of this context's betas: not after another context's loss_grad, nor
+// before any. Bound by latency (21120 weights are 350 KB): a thread's first
 // element, the loss, the step, the bias corrections (reduce_kernel's) and its
 // share of the norm partials are requested together, and the norm is summed by
 // lane exchange. With double-precision powers and 64-bit divisions out of this
@@ -517,7 +524,7 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
     w0 = a.w[i0];
   }
   const int64_t t0 = *a.step_snapshot;
-  const float step_size = a.corr[0], bc2_sqrt = a.corr[1];
+  BiasCorrections bc = *a.corr;
   const double loss = a.stats[0];
   double s = 0.0;
   for (int j = threadIdx.x; j < a.n_norm; j += 256) s += a.norm_partial[j];
@@ -529,6 +536,11 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
     *a.step = skip ? t0 : t0 + 1;
   }
   if (skip) return;
+  if (!(bc.bc1 > 0.0f && bc.beta1 == a.beta1 && bc.beta2 == a.beta2)) {
+    bc.bc1 = (float)bias_correction(a.beta1, t0 + 1);
+    bc.bc2_sqrt = (float)sqrt(bias_correction(a.beta2, t0 + 1));
+  }
+  const float step_size = a.lr / bc.bc1;
   const NetDims d{a.H, a.NH, a.K, a.S, a.E};
   for (int64_t i = i0; i < a.n_weights; i += stride) {
     if (i != i0) {
@@ -539,7 +551,7 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
     }
     const float m = fmaf(a.beta1, m0, (1.0f - a.beta1) * g0);
     const float v = fmaf(a.beta2, v0, (1.0f - a.beta2) * g0 * g0);
-    const float denom = sqrtf(v) / bc2_sqrt + a.adam_eps;
+    const float denom = sqrtf(v) / bc.bc2_sqrt + a.adam_eps;
     const float w = w0 - step_size * (m / denom);
     a.m[i] = m;
     a.v[i] = v;
