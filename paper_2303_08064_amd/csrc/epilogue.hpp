@@ -176,13 +176,17 @@ __device__ __forceinline__ void sample_unit(const QueryLobe& s, float xi0, float
   vz *= inv;
 }
 
-// The mixture pdf at a unit direction: sum_k c_k G_k over the lane's lobes,
-// then the vertex's 4 lanes. No running maximum is needed: the direction was
-// drawn from this mixture, so the lobe that it came from (A_k of at least
-// 2^-24 or so) has a G of about xi0 (2^-24) or more there, and what lies
-// beneath the float range is beneath the sum's rounding.
+// sum_k c_k G_k at a unit direction (the mixture pdf is query_pdf_scale times
+// it), over the lane's lobes, then the vertex's 4 lanes. No running maximum is
+// needed where the sum is above 2^-64: a G beneath the float range (2^-126)
+// loses less than c_k 2^-126 there, and c_k is at most 2^33 at the clamps of
+// lambda and a. The lobe that the direction was drawn from usually sees to
+// that (A_k and G of about 2^-24 at least, for 24-bit uniforms), but not where
+// xi_sel = 0 picked a lobe of any weight, or xi0 = 0 the antipode, where G = 0:
+// a wave with such a vertex takes its sum by the logarithm.
+constexpr float kLinearSumMin = 5.421010862427522e-20f;   // 2^-64
 template <int KQ>
-__device__ __forceinline__ float query_pdf(const QueryLobe (&lb)[KQ], float vx, float vy, float vz, float eps) {
+__device__ __forceinline__ float query_sum(const QueryLobe (&lb)[KQ], float vx, float vy, float vz, float eps) {
 #pragma clang fp contract(off)
   float s = 0.0f;
 #pragma unroll
@@ -192,7 +196,24 @@ __device__ __forceinline__ float query_pdf(const QueryLobe (&lb)[KQ], float vx, 
     // a lobe without density adds nothing, whatever its weight (NaN among them)
     s = fsel(on, fmaf(lb[q].c, __builtin_amdgcn_exp2f(lg), s), s);
   }
-  return quad_sum(s) * query_pdf_scale(eps);
+  return quad_sum(s);
+}
+template <int KQ>
+__device__ __forceinline__ float query_sum_log(const QueryLobe (&lb)[KQ], float vx, float vy, float vz, float eps) {
+#pragma clang fp contract(off)
+  float t[KQ], m = -INFINITY, e = 0.0f;
+#pragma unroll
+  for (int q = 0; q < KQ; ++q) {
+    bool on;
+    const float lg = eval_query_lobe(lb[q], vx, vy, vz, eps, on);
+    t[q] = fsel(on, flog2(lb[q].c) + lg, -INFINITY);
+    m = fmaxf(m, t[q]);
+  }
+  m = quad_max(m);
+#pragma unroll
+  for (int q = 0; q < KQ; ++q) e += __builtin_amdgcn_exp2f(t[q] - m);
+  e = quad_sum(e);
+  return fsel(m == -INFINITY, 0.0f, __builtin_amdgcn_exp2f(m + flog2(e)));
 }
 
 // Records of one 16-vertex block's lobes (optional output of a query); lse:
@@ -276,19 +297,38 @@ __device__ __forceinline__ void query_epilogue(const QueryArgs& a, int64_t v0, i
   }
   float vx, vy, vz;
   sample_unit(ch, xr[1], xr[2], xr[3], a.eps, vx, vy, vz);
-  float pdf = 0.0f;
-#pragma unroll
-  for (int b = 0; b < NBLK; ++b) {
-    float bx = vx, by = vy, bz = vz;
+  // block b's directions, at the lanes that hold its lobes
+  auto at_block = [&](int b, float& bx, float& by, float& bz) {
+    bx = vx;
+    by = vy;
+    bz = vz;
     if constexpr (NBLK > 1) {
       const int src = b * kTileV + c;
       bx = __shfl(vx, src);
       by = __shfl(vy, src);
       bz = __shfl(vz, src);
     }
-    const float q = query_pdf<KQ>(lb[b], bx, by, bz, a.eps);
-    if (NBLK == 1 || g % NBLK == b) pdf = q;
+  };
+  float sum = 0.0f;
+#pragma unroll
+  for (int b = 0; b < NBLK; ++b) {
+    float bx, by, bz;
+    at_block(b, bx, by, bz);
+    const float s = query_sum<KQ>(lb[b], bx, by, bz, a.eps);
+    if (NBLK == 1 || g % NBLK == b) sum = s;
   }
+  if (__any(sum < kLinearSumMin)) {
+    float logsum = 0.0f;
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) {
+      float bx, by, bz;
+      at_block(b, bx, by, bz);
+      const float s = query_sum_log<KQ>(lb[b], bx, by, bz, a.eps);
+      if (NBLK == 1 || g % NBLK == b) logsum = s;
+    }
+    sum = fsel(sum < kLinearSumMin, logsum, sum);
+  }
+  const float pdf = sum * query_pdf_scale(a.eps);
   if (vi_valid && g < NBLK) {
     a.dir_out[vi] = vx;
     a.dir_out[a.ld + vi] = vy;

@@ -6,8 +6,9 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import nasg as onasg
 from paper_2303_08064_amd import synth
-from tests.helpers import CONFIGS, make_guide, to_dev
+from tests.helpers import CONFIGS, ENCODED, make_guide, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +68,50 @@ def test_nan_pair(name, p):
     for a, b in zip(zero[:4], nan[:4]):
         assert torch.equal(a, b)
     assert (zero[4], nan[4]) == (0, 1)
+
+
+@pytest.mark.parametrize("name,B", [(n, 20000) for n in CONFIGS if "nh" not in n] +
+                         [("c3_bf16", 131072 + 100), ("c3_f32", 131072 + 100)])
+def test_unlikely_lobe_beside_a_sharp_one(name, B):
+    """xi_sel = 0 picks lobe 0 however small its weight (here e^-85), xi0 = 0
+    the antipode of its axis. In a ring around a sharp lobe (lambda 148, a 7.4)
+    the density is that lobe's, whose G is below the float range there while
+    the density is not. Against float64 at the returned direction: where log G
+    is -90, at angles of 0.4 (along x) and more, it moves by 180 / angle, some
+    500, times the rounding of the frame and the direction, 1e-6 each."""
+    K = CONFIGS[name][2]
+    g, _ = make_guide(name)
+    raw = np.zeros((8, K), np.float32)
+    raw[2] = raw[4] = 1.0                       # phi = tau = 0
+    raw[5], raw[6], raw[7] = -2.0, -2.0, -300.0
+    raw[:, 0] = (-1.5, 1.0, 0.5, 0.25, 1.0, -2.0, -2.0, -85.0)
+    raw[:, 1] = (1.0, 0.5, 2.0, 0.5, -1.0, 5.0, 2.0, 0.0)
+    mats = g.split(g.w)
+    for m in mats:
+        m.zero_()
+    mats[0][0, 63 if name in ENCODED else 9] = 1.0    # the constant one, handed through
+    for m in mats[1:-1]:
+        m[0, 0] = 1.0
+    mats[-1][:8 * K, 0] = to_dev(raw.reshape(-1))
+    g.repack()
+    rng = synth.rng_for(8)
+    feat, xi = synth.features(B, rng), synth.uniforms(B, rng)
+    xi[0] = 0.0
+    xi[1, ::7] = 0.0
+    d, p = g.query(to_dev(feat), to_dev(xi))
+    out = g.forward_raw(to_dev(feat[:, :1])).cpu().double()[:8 * K, 0]
+    v = d.cpu().double().T
+    lobes = onasg.decode(out.expand(B, 8 * K), K)
+    ref = onasg.mixture_log_pdf(v, lobes).numpy()
+    p = p.cpu().numpy().astype(np.float64)
+    tiny, tol = float(np.log(np.finfo(np.float32).tiny)), 2e-3
+    normal = ref > tiny + tol
+    # directions of which the sharp lobe's share is beneath its float range
+    log_g = onasg.lobe_log_g(v[:, None, :], lobes.z, lobes.x, lobes.lam, lobes.a)[:, 1].numpy()
+    lost = normal & (log_g < tiny) & (onasg.component_log_terms(v, lobes)[:, 1].numpy() > ref - 0.7)
+    assert lost.sum() > 50
+    with np.errstate(divide="ignore"):
+        err = np.abs(np.log(p) - ref)
+    assert np.all(err[normal] <= tol), (err[normal].max(), int((err[normal] > tol).sum()))
+    assert np.all(p[ref < tiny - tol] < 2 * np.finfo(np.float32).tiny)
+    g.close()
