@@ -573,11 +573,14 @@ __global__ __launch_bounds__(256) void large_query_kernel(QueryArgs a) {
     in = load(tile + gridDim.x);
     if constexpr (MODE == 1) {
       if (valid) {
+        // the base is opaque to the compiler, which otherwise keeps an address
+        // per output row across the tile loop (BF16 more than 256 registers,
+        // one workgroup per CU; with it 167: 230000 K = 32 vertices 101 -> 67
+        // us, FP32 443 -> 354)
+        float* base = a.raw_out + (int64_t)(g * KQ) * a.ld + v;
+        asm("" : "+v"(base));
 #pragma unroll
-        for (int t = 0; t < 2 * K; ++t) {
-          const int p = t / KQ, k = g * KQ + t % KQ;
-          a.raw_out[(int64_t)(p * K + k) * a.ld + v] = out[t >> 2][t & 3];
-        }
+        for (int t = 0; t < 2 * K; ++t) base[(int64_t)(t / KQ * K + t % KQ) * a.ld] = out[t >> 2][t & 3];
         if (SEL == 1 && g == 0) a.raw_out[(int64_t)(8 * K) * a.ld + v] = out[N::MTO - 1][0];
       }
     } else {
