@@ -287,33 +287,50 @@ static QueryKernel find_query_kernel(const NetDims& d, int prec, int mode, bool 
   return {nullptr, nullptr, 0, 0, 0};
 }
 
-// One-block or four-block passes, by rounds over 8 waves per CU (two per
-// SIMD), in hundredths of a four-block round (64 vertices a wave). A one-block
-// round (16 vertices a wave) takes about 29 in BF16 and 27 in FP32, a last one
-// of at most half the waves (one per SIMD) 15. A last four-block round of at most half the waves
-// takes 58 in BF16; in FP32, whose chains of 32-cycle MFMAs wait for
-// themselves, as long as a full one.
-// Measured (us, one-block / four-block): K = 16 BF16 777 vertices 5.5 / 13.5,
-// 65536 12.6 / 14.7, 131072 22.0 / 20.9, 300000 46.5 / 43.4; K = 8 FP32 777
-// 8.7 / 41, 98304 35.3 / 43.0, 131072 45.1 / 43.4, 200000 71 / 83.
-// BF16 with K = 4 and 8, which hold three one-block waves per SIMD: one block
-// up to six and seven rounds. K = 8 50000 8.3 / 10.4, 65536 8.6 / 10.6, 100000
-// 12.9 / 14.1, 131072 14.2 / 14.2, 180000 18.9 / 19.3, 229000 24.1 / 25.9,
-// 262144 27.1 / 26.1; K = 4 65536 6.9 / 8.5, 100000 9.1 / 10.4, 180000 13.4 /
-// 13.4, 229000 17.3 / 15.9.
-static bool query_is_small(int64_t B, int num_cus, int K, int prec) {
-  const int64_t wave = 8LL * num_cus;
-  if (prec == 1 && K < 16) return B <= (K == 4 ? 6 : 7) * 16 * wave;
-  const int64_t full1 = B / (16 * wave), rest1 = B - full1 * 16 * wave;
-  const int64_t full4 = B / (64 * wave), rest4 = B - full4 * 64 * wave;
-  const int64_t one = prec == 1 ? 29 : 27;
-  const int64_t last1 = rest1 == 0 ? 0 : (rest1 <= 8 * wave ? 15 : one);
-  const int64_t last4 = rest4 == 0 ? 0 : (prec == 1 && rest4 <= 32 * wave ? 58 : 100);
-  return one * full1 + last1 < 100 * full4 + last4;
+// One-block or four-block passes, by what the batch's rounds cost. With eight
+// waves per CU (two per SIMD) a round of one-block passes takes 128 vertices a
+// CU, one of four-block passes 512; a batch's last round counts as half where
+// one wave per SIMD is enough for it. In thousandths of a four-block round:
+// * BF16, one-block passes: `slope` a half round and an offset, as their rounds
+//   overlap (K = 4 and 8 hold three waves per SIMD);
+// * BF16, four-block passes: 1000 a round and for a last half `first`, less
+//   `drop` for every round before it, but `least` (waves that are out of step
+//   by then fill its idle SIMDs);
+// * with the record store both cost more; past 240 MB of records, the size of
+//   the last-level cache, the four-block passes' longer stores win;
+// * FP32, whose chains of 32-cycle MFMAs wait for themselves: 270 a one-block
+//   round, 150 its half, a last four-block half as long as a full one.
+// Measured (us, one-block / four-block, 256 CUs): K = 16 BF16 49152 vertices
+// 9.3 / 14.7, 65536 10.9 / 14.7, 114688 17.4 / 18.6, 131072 18.9 / 18.8, 180224
+// 25.0 / 27.1, 196608 27.7 / 27.3, 229376 31.2 / 34.9, 327680 43.8 / 40.6,
+// 360448 48.4 / 51.3; with records 65536 14.9 / 21.0, 131072 24.1 / 25.2, 180224
+// 31.1 / 36.0, 262144 43.3 / 45.5, 376832 59.4 / 63.4, 442368 91.5 / 88.5. K = 8
+// 114688 11.9 / 13.4, 131072 14.1 / 13.4, 245760 22.8 / 24.1, 262144 25.4 / 24.4,
+// 475136 43.1 / 45.9, 589824 52.3 / 49.2; with records 131072 17.4 / 18.1, 393216
+// 41.2 / 43.5, 786432 91.3 / 94.5, 983040 139 / 125. K = 4 131072 9.7 / 10.5,
+// 196608 13.8 / 12.5, 229376 15.2 / 16.6, 262144 17.5 / 16.6; with records 196608
+// 16.9 / 16.4, 229376 18.4 / 20.7. FP32 K = 8 777 8.7 / 41, 98304 35.3 / 43.0,
+// 131072 45.1 / 43.4, 200000 71 / 83.
+static bool query_is_small(int64_t B, int num_cus, int K, int prec, bool records) {
+  const int64_t unit = 64LL * num_cus;                          // a one-block half round
+  const int64_t h = (B + unit - 1) / unit;                      // one-block half rounds
+  const int64_t q = (B + 4 * unit - 1) / (4 * unit);            // four-block half rounds
+  if (prec != 1) return 270 * (h / 2) + 150 * (h % 2) < 1000 * ((q + 1) / 2);
+  if (records && B * (9 * 4) * K > 240000000) return false;
+  struct Cost { int slope, offset, first, drop, least; };
+  const Cost c = K == 4   ? (records ? Cost{150, -320, 400, 0, 400} : Cost{157, -350, 350, 0, 350})
+                 : K == 8 ? (records ? Cost{120, 20, 780, 140, 200} : Cost{132, -50, 780, 140, 200})
+                          : (records ? Cost{123, 0, 770, 250, 250} : Cost{128, 0, 770, 250, 250});
+  int64_t four = 1000 * (q / 2);
+  if (q % 2) {
+    const int64_t last = c.first - c.drop * (q / 2);
+    four += last > c.least ? last : c.least;
+  }
+  return c.slope * h + c.offset < four;
 }
 
 hipError_t launch_query(const QueryArgs& a, const NetDims& d, int prec, int mode, hipStream_t st) {
-  const bool small = query_is_small(a.B, a.num_cus, d.K, prec);
+  const bool small = query_is_small(a.B, a.num_cus, d.K, prec, mode == 2);
   const QueryKernel k = find_query_kernel(d, prec, mode, small);
   if (k.nb == 0) return hipErrorInvalidValue;
   const int TV = kTileV * k.nb;   // vertices per wave pass
