@@ -105,7 +105,6 @@ template <int R>
 struct Staged {
   static constexpr int U = R / 16;
   static_assert(R % 16 == 0 && (U % 2 == 1 || U == 2 || U == 4 || U == 8), "rows of a staging buffer");
-  static constexpr int elems(int nv) { return R * nv; }
   __device__ __forceinline__ static int key(int slot) {
     return U == 8 ? (slot & 7) : (U == 4 ? ((slot >> 1) & 3) : (U == 2 ? ((slot >> 2) & 1) : 0));
   }
@@ -136,7 +135,6 @@ struct Staged {
 
 template <int SP>
 struct Rows {
-  static constexpr int elems(int rows) { return rows * SP; }
   __device__ __forceinline__ static uint32_t read_base(const void* buf, int g, int c) {
     return lds_addr(buf) + 2 * (c * SP + 8 * g);
   }

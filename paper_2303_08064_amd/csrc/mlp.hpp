@@ -106,28 +106,6 @@ struct Mlp<H, K, 1, E> {
       return bf16x4{(__bf16)f[0], (__bf16)f[1], (__bf16)f[2], (__bf16)f[3]};
     }
   }
-  // both at once, from any v
-  __device__ __forceinline__ static Input load_input(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
-    Raw r = {};
-    if (valid) r = load_raw(feat, ld, v, g);
-    return input(r, valid, g);
-  }
-
-  __device__ __forceinline__ static bf16x8 operand(const float (&in)[2][4]) {
-    bf16x8 b;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) b[j] = (__bf16)in[j >> 2][j & 3];
-    return b;
-  }
-
-  // h = relu(W_0 x)
-  __device__ __forceinline__ static void layer0(const __bf16* lds, const Input& x, float (&h)[MTH][4], int lane) {
-    layer0_linear(lds, x, h, lane);
-#pragma unroll
-    for (int mt = 0; mt < MTH; ++mt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h[mt][i] = relu(h[mt][i]);
-  }
 
   // Next layer's B operands from a layer's pre-activation accumulators, the
   // ReLU applied to the packed BF16 values (one 16-bit integer max per pair:
@@ -256,28 +234,6 @@ struct Mlp<H, K, 1, E> {
       }
     }
   }
-
-  // out = W in over MT row tiles, W fragments [MT][KBH][64] at `lds`
-  template <int MT>
-  __device__ __forceinline__ static void gemm(const __bf16* lds, const float (&in)[MTH][4], float (&out)[MT][4], int lane) {
-    const bf16x8* frag = reinterpret_cast<const bf16x8*>(lds);
-    bf16x8 b[KBH];
-#pragma unroll
-    for (int kb = 0; kb < KBH; ++kb) {
-      float t[2][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { t[0][i] = in[2 * kb][i]; t[1][i] = in[2 * kb + 1][i]; }
-      b[kb] = operand(t);
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      f32x4 acc = zero4();
-#pragma unroll
-      for (int kb = 0; kb < KBH; ++kb) acc = mfma_bf16_32(frag[(mt * KBH + kb) * 64 + lane], b[kb], acc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[mt][i] = acc[i];
-    }
-  }
 };
 
 // ---------------------------------------------------------------- FP32 ----
@@ -336,6 +292,7 @@ struct Mlp<H, K, 0, E> {
     }
     return in;
   }
+  // both steps at once, from any v
   __device__ __forceinline__ static Input load_input(const float* __restrict__ feat, int64_t ld, int64_t v, bool valid, int g) {
     Raw r = {};
     if (valid) r = load_raw(feat, ld, v, g);
