@@ -19,7 +19,6 @@ __device__ __forceinline__ void lobe_raw(const float (&out)[MTO][4], int q, floa
   }
 }
 
-
 // Weighted NLL of one vertex and its gradient w.r.t. the raw outputs
 // (Sec. 4.2): gs = dL/dlog q = -w/B (0 for padding lanes). Writes dl in the
 // accumulator layout and returns the vertex's log term (log q; with the
@@ -180,7 +179,7 @@ __device__ __forceinline__ void sample_unit(const QueryLobe& s, float xi0, float
 // it), over the lane's lobes, then the vertex's 4 lanes. No running maximum is
 // needed where the sum is above 2^-64: a G beneath the float range (2^-126)
 // loses less than c_k 2^-126 there, and c_k is at most 2^33 at the clamps of
-// lambda and a. The lobe that the direction was drawn from usually sees to
+// lambda and a (and epsilon not above a's). The lobe that the direction was drawn from usually sees to
 // that (A_k and G of about 2^-24 at least, for 24-bit uniforms), but not where
 // xi_sel = 0 picked a lobe of any weight, or xi0 = 0 the antipode, where G = 0:
 // a wave with such a vertex takes its sum by the logarithm.
@@ -258,8 +257,9 @@ __device__ __forceinline__ void query_epilogue(const QueryArgs& a, int64_t v0, i
   const int i = (g % NBLK) * kTileV + c;   // the vertex this lane samples
   const int64_t vi = v0 + i;
   const bool vi_valid = vi < a.B;
-  // one block per pass reads its uniforms from global memory: requested here,
-  // used after the lobes are decoded (the others' are staged in LDS)
+  // one block per pass: its uniforms, in registers (query_kernel) or requested
+  // from global memory here (the streamed kernels) and used after the lobes are
+  // decoded; the other forms' are staged in LDS
   float xr[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   if (NBLK == 1 && vi_valid) {
 #pragma unroll
@@ -276,7 +276,9 @@ __device__ __forceinline__ void query_epilogue(const QueryArgs& a, int64_t v0, i
     // a wave in its forward goes first: its MFMAs and LDS reads then run beside
     // the VALU work of the SIMD's other wave, whose instructions fill the gaps
     // (2^20 vertices: K = 16 134.7 -> 132.6 us, K = 8 90.3 -> 88.3, K = 4 55.2 ->
-    // 53.8; FP32 K = 16 at 2^19 211 -> 208; the other way round K = 16 136.8)
+    // 53.8; FP32 K = 16 at 2^19 211 -> 208; the other way round K = 16 136.8).
+    // In the hidden-64 networks only: the hidden-128 kernels have run the forward
+    // before, and block(b, out) copies its registers
     __builtin_amdgcn_s_setprio(1);
     block(b, out);
     __builtin_amdgcn_s_setprio(0);

@@ -19,8 +19,8 @@ namespace nasg {
 // 16-vertex blocks per wave pass (NB of the kernels below):
 // * 4, the hidden-64 networks' queries of large batches: one sample per lane
 //   (the four blocks' lobes take 144 registers at K = 16, so two waves per
-//   SIMD): BF16 in two workgroups of four waves per CU, FP32 (weights of 64
-//   to 97 KiB) in one of eight;
+//   SIMD): BF16 in two workgroups of four waves per CU, FP32 (weights of up to
+//   61 KiB, K = 4, to 90, K = 16 with selection) in one of eight;
 // * 1, their queries of small batches (query_is_small) and raw forwards;
 // * 2, the hidden-128 network whose 132 KiB of forward weights leave room for
 //   one workgroup per CU: eight waves, every weight fragment read feeds both
@@ -54,9 +54,9 @@ constexpr int kPassRows = kInFeatures + 4;
 constexpr int kPassStage = kPassRows * 64;   // floats per wave and buffer
 
 // Direct-to-LDS copies of a pass's inputs (13 wave instructions, no
-// registers). Lanes past the batch read vertex B - 1 instead (in bounds;
-// their values are never used), so that every wave issues the same number of
-// copies and s_waitcnt can count them.
+// registers). Lanes past the batch read vertex B - 1 instead (in bounds; it is
+// computed and its results are not stored), so that every wave issues the same
+// number of copies and s_waitcnt can count them.
 __device__ __forceinline__ void stage_pass(const QueryArgs& a, int64_t tile, float* buf, int lane) {
   int64_t v = tile * (4 * kTileV) + lane;
   v = v < a.B ? v : a.B - 1;
@@ -94,13 +94,13 @@ __device__ __forceinline__ void stage_pass32(const QueryArgs& a, int64_t tile, f
 // the network has the selection output (row 8K, read by lane group 0 from
 // the extra output tile); E = 1: the encoded input; NB: 16-vertex blocks per
 // wave per pass; NW: waves per workgroup.
-// Bound by VALU issue (the K = 16 BF16 pass of 64 vertices issues 4415 slots,
+// Bound by VALU issue (the K = 16 BF16 pass of 64 vertices issues 4460 slots,
 // 4864 before log K, the log-sum-exp and the base-e scalings went, see
-// decode_lobe_query and query_pdf). Measured: 2^20 K = 16 BF16 queries 145 ->
-// 137 us, K = 8 103 -> 94 us (four blocks, was one), 120000 FP32 K = 8
-// queries with records 54.1 -> 51.4 us, 600000 of the hidden-128 network 111
-// -> 101.5 us (one sample per two lane groups, was per group), 777 K = 4 BF16
-// queries 9.3 -> 4.4 us (one-block passes).
+// decode_lobe_query and query_sum). Measured against one block a pass, the
+// log-sum-exp and loads behind branches: 2^20 K = 16 BF16 queries 145 -> 131 us,
+// K = 8 103 -> 89 us, 120000 FP32 K = 8 queries with records 54.1 -> 48.2 us,
+// 600000 of the hidden-128 network 111 -> 100 us (one sample per two lane
+// groups, was per group), 777 K = 4 BF16 queries 9.3 -> 4.0 us (the kernel).
 template <int H, int K, int PREC, int MODE, int S, int E, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(query_waves_per_eu(NB, MODE, PREC, K))))
 void query_kernel(QueryArgs a) {

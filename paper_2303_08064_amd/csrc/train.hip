@@ -368,9 +368,8 @@ hipError_t launch_train(const TrainArgs& a, int H, int K, int prec, int n_wg, hi
 // gradient norm of the non-finite check). One more block beside them totals the
 // FP64 loss partials (strided per thread, then a fixed tree) and takes the
 // step snapshot and Adam's bias corrections, which therefore wait for nothing.
-// n_weights is a multiple
-// of 4 for every compiled network (checked on the host); at most 256
-// workgroup partials, 512 loss partials.
+// n_weights is a multiple of 4 for every compiled network (checked on the
+// host); at most 256 workgroup partials, 512 loss partials.
 constexpr int kRedW = 64;   // weights per block
 constexpr int kRedQ = 16;   // workgroup groups per block
 constexpr int kRedT = kMaxTrainWG / kRedQ;   // partial rows per group
