@@ -296,8 +296,9 @@ static QueryKernel find_query_kernel(const NetDims& d, int prec, int mode, bool 
 // * BF16, four-block passes: 1000 a round and for a last half `first`, less
 //   `drop` for every round before it, but `least` (waves that are out of step
 //   by then fill its idle SIMDs);
-// * with the record store both cost more; past 240 MB of records, the size of
-//   the last-level cache, the four-block passes' longer stores win;
+// * with the record store both cost more; past 220 MB of records, near the size
+//   of the last-level cache (256 MB), the four-block passes are the safer ones
+//   (K = 16 with selection, 393216 vertices: 78.6 / 72.8 us, without 71.2 / 75.6);
 // * FP32, whose chains of 32-cycle MFMAs wait for themselves: 270 a one-block
 //   round, 150 its half, a last four-block half as long as a full one.
 // Measured (us, one-block / four-block, 256 CUs): K = 16 BF16 49152 vertices
@@ -316,7 +317,7 @@ static bool query_is_small(int64_t B, int num_cus, int K, int prec, bool records
   const int64_t h = (B + unit - 1) / unit;                      // one-block half rounds
   const int64_t q = (B + 4 * unit - 1) / (4 * unit);            // four-block half rounds
   if (prec != 1) return 270 * (h / 2) + 150 * (h % 2) < 1000 * ((q + 1) / 2);
-  if (records && B * (9 * 4) * K > 240000000) return false;
+  if (records && B * (9 * 4) * K > 220000000) return false;
   struct Cost { int slope, offset, first, drop, least; };
   const Cost c = K == 4   ? (records ? Cost{150, -320, 400, 0, 400} : Cost{157, -350, 350, 0, 350})
                  : K == 8 ? (records ? Cost{120, 20, 780, 140, 200} : Cost{132, -50, 780, 140, 200})
